@@ -1,16 +1,42 @@
 // attn_fwd_f32.hip -- fused attention forward for fp32 inputs on gfx950.
 //
-// fp32 has no faster matrix path on this chip (the fp32 matrix and vector
-// peaks are equal), so each lane owns one query row and accumulates with
-// fp32 vector FMAs. A workgroup covers 64 query rows of one (sequence, query
-// head) with four wavefronts that split the key tiles between them (wave w
-// takes tiles lo + w, lo + w + 4, ...), each staging its own key/value tiles
-// through LDS and reading them as broadcasts; the four partial results
-// (running max, sum and O per row) are merged through LDS at the end. The score modifications, the masks with
-// tile skipping, the base-2 online softmax and the ReLU / Sigmoid
-// normalisations are the same as in the bf16 kernel (Eq. 1 and 2 of Section
-// 2.2, Appendix A). On the general mask path each lane derives its row's
-// visible keys (row_vis.h) and the wave visits the union of the rows' tiles.
+// Both products run on the fp32 matrix instruction v_mfma_f32_32x32x2_f32:
+// fp32 operands, products and sums, as vector FMAs would give, at the fp32
+// matrix rate (157 TFLOP/s nominal; a large library product reaches 153 here),
+// where vector FMAs without packed instructions stop at half of that and the
+// LDS broadcasts that feed them at an eighth.
+//
+// A wavefront owns 32 query rows of one query head and walks key tiles of 32.
+//  * Scores are computed transposed, S^T = K Q^T, so a lane owns one query row
+//    (lane % 32) and 16 of the 32 keys: the row max and sum are per-lane
+//    reductions and one exchange with lane ^ 32.
+//  * The contraction order over the head dim is free, so lane half h takes the
+//    dims 8c + 4h .. 8c + 4h + 3 of chunk c: one 16-byte load of K (global) and
+//    one of Q (LDS, stored in this fragment order) feed four products.
+//  * The accumulator of half h holds keys (r & 3) + 8 (r >> 2) + 4 h in
+//    register r, which is the B operand of O^T = V^T P^T as it stands when the
+//    A operand takes the same key: each half loads that key's V row.
+//  * Row i of the 32-row block d of O^T is head dim (D / 32) i + d, so one
+//    16-byte (D = 64: 8-byte) load of V feeds all blocks and an output row is
+//    stored in 16-byte (8-byte) pieces.
+//  * K and V go straight from memory to registers, each tile's K while the
+//    previous tile's P V products run and its V while its own K Q^T products
+//    run: the products of a tile take 64 D clocks of a SIMD, longer than the
+//    loads, and nothing waits at a barrier.
+// The four wavefronts of a workgroup take the same 32 rows and every fourth
+// key tile each (wave w tiles lo + w, lo + w + 4, ...); their partial results
+// (running max, sum and O per row) are merged through LDS. Bound by the matrix
+// cores and, at up to a few thousand rows, by how evenly the rows' keys fill
+// the chip, so the work items are kept small: 128-row workgroups (one 32-row
+// block and all keys per wave) measured 4 % faster only for 2 x 16 heads of
+// 4096 rows without a mask (2090 against 2184 us) and slower elsewhere (2 x 16
+// causal heads of 1000 rows at D = 128: 139 against 100 us), and sum longer
+// chains (relative error 1.3e-6 against 7.1e-7). The vector-FMA kernel before
+// took 411 us (20 TFLOP/s) there. The score modifications, the masks with tile skipping, the base-2 online softmax
+// and the ReLU / Sigmoid normalisations are the same as in the bf16 kernel (Eq.
+// 1 and 2 of Section 2.2, Appendix A). On the general mask path each lane
+// derives its row's visible keys (row_vis.h) and the wave visits the tiles
+// that some row of it sees.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -23,13 +49,12 @@ namespace attn {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int BM = 64;     // query rows per workgroup (one per lane of every wave)
 constexpr int NW = 4;      // wavefronts, each with a share of the key tiles
 constexpr int NT = 64 * NW;
-
-// Keys per tile: the four waves' double K/V tiles fit 64 KiB of LDS.
-constexpr int key_tile(int d) { return d == 128 ? 16 : 32; }
+constexpr int BM = 32;     // query rows per workgroup (every wavefront the same ones)
+constexpr int BN = 32;     // keys per tile
 
 __device__ __forceinline__ int wave_min(int x)
 {
@@ -45,28 +70,72 @@ __device__ __forceinline__ int wave_max(int x)
     return x;
 }
 
+// Lanes l and l ^ 32 hold the two halves of the same query row.
+__device__ __forceinline__ float pair_max(float x)
+{
+    auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x),
+                                              __builtin_bit_cast(uint32_t, x), false, false);
+    return __builtin_fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]),
+                           __builtin_bit_cast(float, (uint32_t)r[1]));
+}
+
+__device__ __forceinline__ float pair_sum(float x)
+{
+    auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x),
+                                              __builtin_bit_cast(uint32_t, x), false, false);
+    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+
+// Buffer descriptor of one (sequence, head) slice: rows past its end read as zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t slice_rsrc(const float* base, int rows, int64_t stride,
+                                                             int d)
+{
+    const uint32_t bytes = rows <= 0 ? 0u : (uint32_t)((((int64_t)rows - 1) * stride + d) * 4);
+    // dword3 0x00020000: 32-bit untyped data format, no swizzle (gfx9 family)
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, (int)bytes, 0x00020000);
+}
+
 template <int D, bool SOFTCAP, int BIAS, int NORM, bool GEN>
-__global__ __launch_bounds__(NT) void attn_fwd_f32_kernel(AttnParams p)
+__global__ __launch_bounds__(NT, 2) void attn_fwd_f32_kernel(AttnParams p)
 {
     constexpr bool SOFTMAX = NORM == kNormSoftmax;
-    constexpr int BN = key_tile(D);
-    constexpr int KV_BYTES = NW * 2 * BN * D * 4;         // per-wave K and V tiles
-    constexpr int MERGE_BYTES = 2 * BM * (D + 2) * 4;      // two partial results
-    __shared__ __attribute__((aligned(16))) float qs[BM][D + 4];  // padded rows
-    __shared__ __attribute__((aligned(16))) char lds[KV_BYTES > MERGE_BYTES ? KV_BYTES : MERGE_BYTES];
+    constexpr bool MODS = SOFTCAP || BIAS != kBiasNone;
+    constexpr int QC = D / 8;    // 16-byte chunks of Q and K per lane
+    constexpr int DB = D / 32;   // 32-row blocks of O^T
+    typedef float vrow_t __attribute__((ext_vector_type(DB)));
+    // Q fragments [chunk][lane], then (after the key loop) the waves' partial O
+    // [wave][register][lane]
+    constexpr int WAVE_BYTES = BM * D * 4;
+    __shared__ __attribute__((aligned(16))) char lds[NW * WAVE_BYTES];
+    __shared__ float ml[NW][BM][2];
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int li = lane & 31, lh = lane >> 5;
     if constexpr (kLdsPoison) {
-        for (int i = tid; i < (int)(sizeof(qs) / 4); i += NT) (&qs[0][0])[i] = __builtin_bit_cast(float, ~0u);
-        for (int i = tid; i < (int)(sizeof(lds) / 4); i += NT)
-            reinterpret_cast<uint32_t*>(lds)[i] = ~0u;
+        for (int i = tid; i < (int)(sizeof(lds) / 4); i += NT) reinterpret_cast<uint32_t*>(lds)[i] = ~0u;
+        for (int i = tid; i < (int)(sizeof(ml) / 4); i += NT)
+            (&ml[0][0][0])[i] = __builtin_bit_cast(float, ~0u);
         __syncthreads();
     }
-    const int nbh = p.batch * p.hq;
-    const int w = blockIdx.x;
-    const int qt = p.q_order ? w / nbh : p.num_q_tiles - 1 - w / nbh;
-    const int b = (w % nbh) / p.hq, hq = (w % nbh) % p.hq;
+    // Work item: (sequence, query head, query tile), longest tiles first. With
+    // map_mode 1 the query heads of a kv group go to one XCD (ids are dealt
+    // round-robin over the 8 XCDs) and read its K/V through one L2.
+    int b, hq, qt;
+    {
+        const int w = blockIdx.x, nbh = p.batch * p.hq;
+        int t = w / nbh, r = w - t * nbh;
+        if (p.map_mode == 1) {
+            const int x = r & 7, k = r >> 3, gpx = (p.batch * p.hkv) >> 3;
+            const int h = k / gpx, g = x + 8 * (k - h * gpx);  // head in group, kv group
+            b = g / p.hkv;
+            hq = (g - b * p.hkv) * p.group + h;
+        } else {
+            b = r / p.hq;
+            hq = r - b * p.hq;
+        }
+        qt = p.q_order ? t : p.num_q_tiles - 1 - t;
+    }
 
     int lq, lk;
     int64_t qrow0 = 0, krow0 = 0;
@@ -86,51 +155,113 @@ __global__ __launch_bounds__(NT) void attn_fwd_f32_kernel(AttnParams p)
     const float* kb = static_cast<const float*>(p.k);
     const float* vb = static_cast<const float*>(p.v);
     float* ob = static_cast<float*>(p.o);
-    int64_t qoff, koff, voff, ooff;
+    int64_t ooff;
     if (p.cu_q) {
-        qoff = qrow0 * p.sq_s + (int64_t)hq * p.sq_h;
+        qb += qrow0 * p.sq_s + (int64_t)hq * p.sq_h;
+        kb += krow0 * p.sk_s + (int64_t)hkv * p.sk_h;
+        vb += krow0 * p.sv_s + (int64_t)hkv * p.sv_h;
         ooff = qrow0 * p.so_s + (int64_t)hq * p.so_h;
-        koff = krow0 * p.sk_s + (int64_t)hkv * p.sk_h;
-        voff = krow0 * p.sv_s + (int64_t)hkv * p.sv_h;
     } else {
-        qoff = (int64_t)b * p.sq_b + (int64_t)hq * p.sq_h;
+        qb += (int64_t)b * p.sq_b + (int64_t)hq * p.sq_h;
+        kb += (int64_t)b * p.sk_b + (int64_t)hkv * p.sk_h;
+        vb += (int64_t)b * p.sv_b + (int64_t)hkv * p.sv_h;
         ooff = (int64_t)b * p.so_b + (int64_t)hq * p.so_h;
-        koff = (int64_t)b * p.sk_b + (int64_t)hkv * p.sk_h;
-        voff = (int64_t)b * p.sv_b + (int64_t)hkv * p.sv_h;
     }
+    const int qi = q0 + li;
 
-    // Q rows into LDS, all four waves cooperating.
-    for (int e = tid; e < BM * (D / 4); e += NT) {
-        const int r = e / (D / 4), c = e % (D / 4);
-        f32x4 x = {0.f, 0.f, 0.f, 0.f};
-        if (q0 + r < lq) x = *reinterpret_cast<const f32x4*>(qb + qoff + (int64_t)(q0 + r) * p.sq_s + 4 * c);
-        *reinterpret_cast<f32x4*>(&qs[r][4 * c]) = x;
-    }
-    __syncthreads();
-
-    const int qi = q0 + lane;  // every wave covers the same 64 rows
-    // this sequence's index-mask layout (one shared by all when the stride is 0)
+    // Visible keys of this lane's row, the key tiles this wave may visit, and
+    // the tiles every row sees whole.
     const int32_t* gtok = p.gtok ? p.gtok + (int64_t)b * p.gtok_stride : nullptr;
     const int32_t* seg = p.seg ? p.seg + (int64_t)b * p.seg_stride : nullptr;
     RowVis rv = {0, 1, 0};
-    int t_lo, t_hi;  // key tiles visited
+    int t_lo, t_hi;
+    TilePlan gp = {0, 0, 0, 0};
+    int pmin = 0, lomax = 0, himin = 0;  // GEN: bounds of the fully visible tiles
     if constexpr (GEN) {
         if (qi < lq)
             rv = gtok ? row_vis_listed(p.band, gtok, p.num_global, qi, lq, lk)
                       : row_visibility(p.mask_kind, p.band, p.num_global, seg, p.num_seg,
                                        p.query_start, qi, lq, lk);
-        const bool any = rv.pfx > 0 || rv.jlo <= rv.jhi;
+        const bool band = rv.jlo <= rv.jhi, any = rv.pfx > 0 || band;
         const int first = any ? (rv.pfx > 0 ? 0 : rv.jlo) : 0x3fffffff;
-        const int last = any ? (rv.jlo <= rv.jhi ? rv.jhi : rv.pfx - 1) : -1;
+        const int last = any ? (band ? rv.jhi : rv.pfx - 1) : -1;
         t_lo = __builtin_amdgcn_readfirstlane(wave_min(first)) / BN;
         t_hi = __builtin_amdgcn_readfirstlane(wave_max(last));
         t_hi = t_hi < 0 ? t_lo : t_hi / BN + 1;
+        const bool row = qi < lq;  // rows past the end take no part
+        pmin = __builtin_amdgcn_readfirstlane(wave_min(row ? rv.pfx : 0x3fffffff));
+        lomax = __builtin_amdgcn_readfirstlane(wave_max(row ? (band ? rv.jlo : 0x3fffffff) : 0));
+        himin = __builtin_amdgcn_readfirstlane(wave_min(row ? (band ? rv.jhi : -1) : 0x3fffffff));
     } else {
         if (qi < lq) band_row(p.band, qi, lq, lk, &rv.jlo, &rv.jhi);
-        const TilePlan gp = plan_tiles(p.band, q0, BM, lq, lk, BN);
+        gp = plan_tiles(p.band, q0, BM, lq, lk, BN);
         t_lo = gp.lo;
         t_hi = gp.hi;
     }
+    auto full_tile = [&](int kt) __attribute__((always_inline)) -> bool {
+        if constexpr (GEN) {
+            const int j0 = kt * BN;
+            return j0 + BN <= pmin || (lomax <= j0 && j0 + BN - 1 <= himin);
+        }
+        return kt >= gp.full_lo && kt < gp.full_hi;
+    };
+    // this wave's next tile, from kt on, that some row sees
+    auto next_tile = [&](int kt) __attribute__((always_inline)) -> int {
+        if constexpr (GEN) {
+            while (kt < t_hi) {
+                const int j0 = kt * BN;
+                const bool hit = (rv.jlo <= rv.jhi && rv.jhi >= j0 && rv.jlo <= j0 + BN - 1) || j0 < rv.pfx;
+                if (__builtin_amdgcn_ballot_w64(hit)) break;
+                kt += NW;
+            }
+        }
+        return kt;
+    };
+
+    // K and V rows: 32-bit byte offsets inside the slice. A slice of at most
+    // one row may have any row stride; the rows past it must not fold onto it.
+    const __amdgpu_buffer_rsrc_t krs = slice_rsrc(kb, lk, p.sk_s, D);
+    const __amdgpu_buffer_rsrc_t vrs = slice_rsrc(vb, lk, p.sv_s, D);
+    const uint32_t krow = (uint32_t)(lk > 1 ? p.sk_s * 4 : D * 4);
+    const uint32_t vrow = (uint32_t)(lk > 1 ? p.sv_s * 4 : D * 4);
+    f32x4 kf[QC];
+    vrow_t vf[16];
+    // 16-byte chunk c of this lane's K row at byte offset `off`; V row of the
+    // key of accumulator register r at position key(i), i its index in the tile
+    auto load_k = [&](uint32_t off, int c) __attribute__((always_inline)) {
+        kf[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(krs, off + 32 * c, 0, 0));
+    };
+    auto load_v = [&](auto key, int r) __attribute__((always_inline)) {
+        const uint32_t off = (uint32_t)key((r & 3) + 8 * (r >> 2) + 4 * lh) * vrow + DB * 4 * li;
+        if constexpr (DB == 4)
+            vf[r] = __builtin_bit_cast(vrow_t, __builtin_amdgcn_raw_buffer_load_b128(vrs, off, 0, 0));
+        else
+            vf[r] = __builtin_bit_cast(vrow_t, __builtin_amdgcn_raw_buffer_load_b64(vrs, off, 0, 0));
+    };
+    auto k_offset = [&](int key) __attribute__((always_inline)) -> uint32_t {
+        return (uint32_t)key * krow + 16 * lh;
+    };
+
+    int kt = next_tile(t_lo + wave);
+    if (kt < t_hi) {
+        const uint32_t off = k_offset(kt * BN + li);
+#pragma unroll
+        for (int c = 0; c < QC; ++c) load_k(off, c);
+    }
+
+    // Q rows into LDS in fragment order, the four waves sharing the work; rows
+    // past the end are zero.
+    f32x4* qs = reinterpret_cast<f32x4*>(lds) + lane;
+    {
+        const __amdgpu_buffer_rsrc_t qrs = slice_rsrc(qb, lq, p.sq_s, D);
+        const uint32_t off = qi < lq ? (uint32_t)((int64_t)qi * p.sq_s * 4) + 16 * lh : 0xffff0000u;
+#pragma unroll
+        for (int i = 0; i < QC / NW; ++i) {
+            const int c = wave * (QC / NW) + i;
+            qs[c * 64] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(qrs, off + 32 * c, 0, 0));
+        }
+    }
+
     const int ip = qi + (lk - lq);
     // relative-position reference (see score_u): first visible key for softmax
     int jref = SOFTMAX ? (rv.pfx > 0 ? 0 : rv.jlo) : ip;
@@ -144,179 +275,176 @@ __global__ __launch_bounds__(NT) void attn_fwd_f32_kernel(AttnParams p)
         if (p.slopes) bias_abs = -p.slopes[hq] * p.unit;
     if constexpr (BIAS == kBiasRelPos || BIAS == kBiasGeneral)
         if (p.relpos) bias_lin = p.unit;
-    constexpr bool MODS = SOFTCAP || BIAS != kBiasNone;
-    float o[D];
+    f32x16 o[DB];
 #pragma unroll
-    for (int d = 0; d < D; ++d) o[d] = 0.0f;
-    float m_run = -__builtin_inff(), l_run = 0.0f;
+    for (int d = 0; d < DB; ++d) o[d] = f32x16{};
+    float m_run = -__builtin_inff(), l_run = 0.0f;  // l: this lane's keys only
+    __syncthreads();
 
-    // This wave's K and V tiles; only this wave touches them, so ordering its
-    // own LDS writes and reads needs a fence, not a workgroup barrier.
-    float (*ks)[D] = reinterpret_cast<float (*)[D]>(lds + wave * 2 * BN * D * 4);
-    float (*vs)[D] = reinterpret_cast<float (*)[D]>(lds + (wave * 2 + 1) * BN * D * 4);
-    // Scores, mask, online softmax and P V for the BN keys in ks / vs; key t
-    // of the tile sits at position jpos(t) and is visible iff vis(t).
-    auto consume = [&](auto jpos, auto vis) __attribute__((always_inline)) {
-        float s[BN];
+    // S^T = K Q^T of the tile in kf, loading the tile's V rows: half of them
+    // ahead of the products, the others as the K chunks are used up, which
+    // keeps the registers of both within two wavefronts per SIMD.
+    auto scores = [&](auto key) __attribute__((always_inline)) -> f32x16 {
+        f32x16 s = {};
 #pragma unroll
-        for (int j = 0; j < BN; ++j) s[j] = 0.0f;
+        for (int r = 0; r < 8; ++r) load_v(key, r);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int c = 0; c < D / 4; ++c) {
-            f32x4 qx = *reinterpret_cast<const f32x4*>(&qs[lane][4 * c]);
+        for (int c = 0; c < QC; ++c) {
+            const f32x4 q = qs[c * 64];
 #pragma unroll
-            for (int j = 0; j < BN; ++j) {
-                f32x4 kx = *reinterpret_cast<const f32x4*>(&ks[j][4 * c]);
-                s[j] = __builtin_fmaf(qx[0], kx[0], s[j]);
-                s[j] = __builtin_fmaf(qx[1], kx[1], s[j]);
-                s[j] = __builtin_fmaf(qx[2], kx[2], s[j]);
-                s[j] = __builtin_fmaf(qx[3], kx[3], s[j]);
-            }
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[c][e], q[e], s, 0, 0, 0);
+            if (c < 8) load_v(key, 8 + c);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        float mx = -__builtin_inff();
+        return s;
+    };
+    // Score mods and mask. The key of register r sits at position jpos(i) and is
+    // visible iff vis(i), i its index in the tile.
+    auto modify = [&](f32x16& s, auto jpos, auto vis) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < BN; ++j) {
-            float x = MODS ? score_u<SOFTCAP, BIAS>(s[j], p.scale_u, p.softcap_pre, p.softcap_post_u,
-                                                    bias_abs, bias_lin, ip, jref, jpos(j))
-                           : s[j] * p.scale_u;
-            if (!vis(j)) x = -__builtin_inff();
-            s[j] = x;
-            mx = __builtin_fmaxf(mx, x);
+        for (int r = 0; r < 16; ++r) {
+            const int i = (r & 3) + 8 * (r >> 2) + 4 * lh;
+            float x = MODS ? score_u<SOFTCAP, BIAS>(s[r], p.scale_u, p.softcap_pre, p.softcap_post_u,
+                                                    bias_abs, bias_lin, ip, jref, jpos(i))
+                           : s[r] * p.scale_u;
+            if (!vis(i)) x = -__builtin_inff();
+            s[r] = x;
         }
-        float alpha = 1.0f, m_new = m_run, m_use = 0.0f;
+    };
+    // Online softmax (or activation): scores to P.
+    auto normalise = [&](f32x16& s) __attribute__((always_inline)) {
         if constexpr (SOFTMAX) {
+            float mx = s[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mx = __builtin_fmaxf(mx, s[r]);
             // A row that has seen no key yet (m_run = -inf) and sees none of
-            // this tile either (a gathered tile of global keys all inside its
-            // band or past the end) keeps m = -inf with O and l at 0: the
+            // this tile either keeps m = -inf with O and l at 0: the
             // exponentials take 0 in place of the max, where
             // exp2(-inf - (-inf)) would be NaN.
-            m_new = __builtin_fmaxf(m_run, mx);
-            m_use = m_new == -__builtin_inff() ? 0.0f : m_new;
-            alpha = __builtin_amdgcn_exp2f(m_run - m_use);  // 0 when only m_run = -inf
-            m_run = m_new;
-            l_run *= alpha;
+            const float m_new = __builtin_fmaxf(m_run, pair_max(mx));
+            const float m_use = m_new == -__builtin_inff() ? 0.0f : m_new;
+            if (__builtin_amdgcn_ballot_w64(m_new > m_run)) {
+                const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);  // 0 when m_run = -inf
+                m_run = m_new;
+                l_run *= alpha;
 #pragma unroll
-            for (int d = 0; d < D; ++d) o[d] *= alpha;
-        }
+                for (int d = 0; d < DB; ++d)
 #pragma unroll
-        for (int j = 0; j < BN; ++j) {
-            float pe;
-            if constexpr (SOFTMAX) {
-                pe = __builtin_amdgcn_exp2f(s[j] - m_use);
-                l_run += pe;
-            } else {
-                pe = activation<NORM>(s[j]);  // the 1/L comes at the end
+                    for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
             }
 #pragma unroll
-            for (int c = 0; c < D / 4; ++c) {
-                f32x4 vx = *reinterpret_cast<const f32x4*>(&vs[j][4 * c]);
-                o[4 * c + 0] = __builtin_fmaf(pe, vx[0], o[4 * c + 0]);
-                o[4 * c + 1] = __builtin_fmaf(pe, vx[1], o[4 * c + 1]);
-                o[4 * c + 2] = __builtin_fmaf(pe, vx[2], o[4 * c + 2]);
-                o[4 * c + 3] = __builtin_fmaf(pe, vx[3], o[4 * c + 3]);
+            for (int r = 0; r < 16; ++r) {
+                s[r] = __builtin_amdgcn_exp2f(s[r] - m_use);
+                l_run += s[r];
             }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = activation<NORM>(s[r]);  // the 1/L comes at the end
         }
     };
-    // K and V rows at positions key(r) (r < BN) into this wave's tiles; rows at
-    // or past the sequence end are zero.
-    auto stage = [&](auto key) __attribute__((always_inline)) {
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // previous tile fully read
+    // O^T += V^T P^T of the tile in vf, loading the next tile's K (`koff`: its
+    // rows' byte offset; past the slice's end the loads return zeros) likewise.
+    auto accumulate = [&](const f32x16& pr, uint32_t koff) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < BN * D / 4 / 64; ++i) {
-            int e = i * 64 + lane;
-            int r = e / (D / 4), c = e % (D / 4);
-            const int j = key(r);
-            f32x4 kx = {0.f, 0.f, 0.f, 0.f}, vx = {0.f, 0.f, 0.f, 0.f};
-            if (j < lk) {
-                kx = *reinterpret_cast<const f32x4*>(kb + koff + (int64_t)j * p.sk_s + 4 * c);
-                vx = *reinterpret_cast<const f32x4*>(vb + voff + (int64_t)j * p.sv_s + 4 * c);
-            }
-            *reinterpret_cast<f32x4*>(&ks[r][4 * c]) = kx;
-            *reinterpret_cast<f32x4*>(&vs[r][4 * c]) = vx;
+        for (int c = 0; c < QC / 2; ++c) load_k(koff, c);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+#pragma unroll
+            for (int d = 0; d < DB; ++d)
+                o[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[r][d], pr[r], o[d], 0, 0, 0);
+            if (r < QC / 2) load_k(koff, QC / 2 + r);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // tile written
     };
-    for (int kt = t_lo + wave; kt < t_hi; kt += NW) {
-        const int j0 = kt * BN;
-        stage([&](int r) { return j0 + r; });
-        const bool band_hit = rv.jlo <= rv.jhi && rv.jhi >= j0 && rv.jlo <= j0 + BN - 1;
-        if (!band_hit && j0 >= rv.pfx) continue;  // row sees none of the tile
-        const bool full = j0 + BN <= rv.pfx || (rv.jlo <= j0 && j0 + BN - 1 <= rv.jhi);
-        consume([&](int j) { return j0 + j; }, [&](int j) { return full || row_sees(rv, j0 + j); });
+    constexpr uint32_t kPastEnd = 0xffff0000u;  // beyond every slice (all are below 2 GiB)
+
+    while (kt < t_hi) {
+        const int j0 = kt * BN, nt = next_tile(kt + NW);
+        f32x16 s = scores([&](int i) { return j0 + i; });
+        if (full_tile(kt))
+            modify(s, [&](int i) { return j0 + i; }, [](int) { return true; });
+        else
+            modify(s, [&](int i) { return j0 + i; }, [&](int i) { return row_sees(rv, j0 + i); });
+        normalise(s);
+        __builtin_amdgcn_sched_barrier(0);
+        accumulate(s, nt < t_hi ? k_offset(nt * BN + li) : kPastEnd);
+        kt = nt;
     }
     // A listed global set (global sliding window): its keys outside the row's
     // band, BN list entries per tile, the waves taking turns.
     if (GEN && gtok) {
         const int ng = p.num_global;
         for (int g0 = wave * BN; g0 < ng; g0 += NW * BN) {
-            auto key = [&](int r) { return g0 + r < ng ? min(gtok[g0 + r], lk) : lk; };
-            stage(key);
-            consume(key, [&](int j) {
-                const int kj = key(j);
+            auto key = [&](int i) { return g0 + i < ng ? min(gtok[g0 + i], lk) : lk; };
+            const uint32_t off = k_offset(key(li));
+#pragma unroll
+            for (int c = 0; c < QC; ++c) load_k(off, c);
+            f32x16 s = scores(key);
+            modify(s, key, [&](int i) {
+                const int kj = key(i);
                 return qi < lq && kj < lk && !(kj >= rv.jlo && kj <= rv.jhi);
             });
+            normalise(s);
+            accumulate(s, kPastEnd);
         }
     }
 
-    // Merge the four partial results: waves 1 and 3 into 0 and 2, then 2 into 0.
-    // A partial (m, l, O) with m = -inf saw no key and contributes nothing.
-    float* mb = reinterpret_cast<float*>(lds);
-    auto publish = [&](int slot) {
-        float* row = mb + (slot * BM + lane) * (D + 2);
-#pragma unroll
-        for (int d = 0; d < D; ++d) row[d] = o[d];
-        row[D] = m_run;
-        row[D + 1] = l_run;
-    };
-    auto absorb = [&](int slot) {
-        const float* row = mb + (slot * BM + lane) * (D + 2);
-        if constexpr (SOFTMAX) {
-            const float m_o = row[D], l_o = row[D + 1];
-            const float m_new = __builtin_fmaxf(m_run, m_o);
-            const float a = m_run == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_new);
-            const float c = m_o == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f(m_o - m_new);
-            m_run = m_new;
-            l_run = a * l_run + c * l_o;
-#pragma unroll
-            for (int d = 0; d < D; ++d) o[d] = a * o[d] + c * row[d];
-        } else {
-#pragma unroll
-            for (int d = 0; d < D; ++d) o[d] += row[d];
+    // Merge the four partial results: every wave scales its O to the common
+    // running max, and wave w adds up registers 4w .. 4w + 3 of all of them. A
+    // partial with m = -inf saw no key and contributes zeros.
+    float l_tot = pair_sum(l_run), m_tot = -__builtin_inff();
+    vrow_t* part = reinterpret_cast<vrow_t*>(lds) + lane;
+    if constexpr (SOFTMAX) {
+        if (lh == 0) {
+            ml[wave][li][0] = m_run;
+            ml[wave][li][1] = l_tot;
         }
-    };
-    __syncthreads();  // every wave is done with its K/V tiles
-    if (wave == 1) publish(0);
-    if (wave == 3) publish(1);
-    __syncthreads();
-    if (wave == 0) absorb(0);
-    if (wave == 2) absorb(1);
-    __syncthreads();
-    if (wave == 2) publish(0);
-    __syncthreads();
-    if (wave != 0) return;
-    absorb(0);
-
-    if (qi < lq) {
-        float inv;
-        if constexpr (SOFTMAX)
-            inv = l_run > 0.0f ? 1.0f / l_run : 0.0f;
-        else
-            inv = lk > 0 ? 1.0f / (float)lk : 0.0f;
-        float* dst = ob + ooff + (int64_t)qi * p.so_s;
+    }
+    __syncthreads();  // also: every wave is done with Q
+    float w = 1.0f;
+    if constexpr (SOFTMAX) {
 #pragma unroll
-        for (int c = 0; c < D / 4; ++c) {
-            f32x4 x = {o[4 * c] * inv, o[4 * c + 1] * inv, o[4 * c + 2] * inv, o[4 * c + 3] * inv};
-            *reinterpret_cast<f32x4*>(dst + 4 * c) = x;
+        for (int k = 0; k < NW; ++k) m_tot = __builtin_fmaxf(m_tot, ml[k][li][0]);
+        l_tot = 0.0f;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            const float mk = ml[k][li][0];
+            if (mk != -__builtin_inff()) l_tot += ml[k][li][1] * __builtin_amdgcn_exp2f(mk - m_tot);
         }
-        if (SOFTMAX && p.lse) {
-            float lse = -__builtin_inff();
-            if (l_run > 0.0f) {
-                lse = (m_run + __builtin_log2f(l_run)) * kLn2;
-                if (bias_lin != 0.0f) lse += (float)(ip - jref);
-            }
-            int64_t idx = p.cu_q ? (int64_t)hq * p.total_q + qrow0 + qi
-                                 : ((int64_t)b * p.hq + hq) * lq + qi;
-            p.lse[idx] = lse;
+        w = m_run == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_tot);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        vrow_t x;
+#pragma unroll
+        for (int d = 0; d < DB; ++d) x[d] = o[d][r] * w;
+        part[(wave * 16 + r) * 64] = x;
+    }
+    __syncthreads();
+    if (qi >= lq) return;
+    float inv;
+    if constexpr (SOFTMAX)
+        inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
+    else
+        inv = lk > 0 ? 1.0f / (float)lk : 0.0f;
+    float* dst = ob + ooff + (int64_t)qi * p.so_s + DB * (8 * wave + 4 * lh);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {  // register 4 wave + e: row 8 wave + 4 lh + e of each block
+        const int r = 4 * wave + e;
+        const vrow_t x = (part[r * 64] + part[(16 + r) * 64]) + (part[(32 + r) * 64] + part[(48 + r) * 64]);
+        *reinterpret_cast<vrow_t*>(dst + DB * e) = x * inv;
+    }
+    if (SOFTMAX && p.lse && wave == 0 && lh == 0) {
+        float lse = -__builtin_inff();
+        if (l_tot > 0.0f) {
+            lse = (m_tot + __builtin_log2f(l_tot)) * kLn2;
+            if (bias_lin != 0.0f) lse += (float)(ip - jref);
         }
+        int64_t idx = p.cu_q ? (int64_t)hq * p.total_q + qrow0 + qi
+                             : ((int64_t)b * p.hq + hq) * lq + qi;
+        p.lse[idx] = lse;
     }
 }
 
