@@ -234,6 +234,22 @@ typedef struct attn_variant_desc {
 int attn_fwd(const void *q, const void *k, const void *v, void *out, float *lse,
              const attn_variant_desc *desc);
 
+/*
+ * attn_fwd with a caller-provided device workspace. When a call has too few
+ * query rows to fill the GPU, the keys of each row are split over workgroups,
+ * which leave partial results in the workspace for a second, small kernel on
+ * the same stream. attn_workspace_bytes returns the bytes the call described
+ * by `desc` can use (0: none; negative: an attn_status_t). With a NULL or
+ * smaller workspace the call is computed without the split (attn_fwd is that
+ * call); the results agree to rounding. The workspace needs 16-byte alignment
+ * (ATTN_ERR_ALIGNMENT otherwise) and no initialisation, holds nothing between
+ * calls, and must stay valid, and unused by other streams, until the work on
+ * desc->stream has completed.
+ */
+int64_t attn_workspace_bytes(const attn_variant_desc *desc);
+int attn_fwd_ws(const void *q, const void *k, const void *v, void *out, float *lse,
+                const attn_variant_desc *desc, void *workspace, int64_t workspace_bytes);
+
 /* Static description of an error code (never NULL). */
 const char *attn_status_string(int status);
 

@@ -225,7 +225,11 @@ def fwd(q, k, v, *, causal: bool = False, window=None, alibi_slopes=None, softca
                   segment_starts=segment_starts, query_start=query_start,
                   relative_position=relative_position, norm=norm, validate=validate,
                   heads_per_wg=heads_per_wg, order=order, chunk=chunk, log=log)
-    status = lib.attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
-                          lse.data_ptr() if lse is not None else None, ctypes.byref(d))
+    # (a negative size is an error that the call itself reports)
+    nbytes = lib.attn_workspace_bytes(ctypes.byref(d))
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device) if nbytes > 0 else None
+    status = lib.attn_fwd_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
+                             lse.data_ptr() if lse is not None else None, ctypes.byref(d),
+                             ws.data_ptr() if ws is not None else None, nbytes)
     check(status, lib)
     return (out, lse) if return_lse else out

@@ -34,8 +34,8 @@ STATUS = {
 }
 STATUS_CODE = {v: k for k, v in STATUS.items()}
 
-EXPORTED = ("attn_fwd", "attn_status_string", "attn_abi_version", "attn_plan_tiles",
-            "attn_row_range")
+EXPORTED = ("attn_fwd", "attn_fwd_ws", "attn_workspace_bytes", "attn_status_string", "attn_abi_version",
+            "attn_plan_tiles", "attn_row_range")
 
 
 class AttnVariantDesc(ctypes.Structure):
@@ -108,6 +108,11 @@ def load(path: str = LIB_PATH):
     lib = ctypes.CDLL(path)
     lib.attn_fwd.restype = ctypes.c_int
     lib.attn_fwd.argtypes = [ctypes.c_void_p] * 5 + [ctypes.POINTER(AttnVariantDesc)]
+    lib.attn_fwd_ws.restype = ctypes.c_int
+    lib.attn_fwd_ws.argtypes = [ctypes.c_void_p] * 5 + [ctypes.POINTER(AttnVariantDesc),
+                                                        ctypes.c_void_p, ctypes.c_int64]
+    lib.attn_workspace_bytes.restype = ctypes.c_int64
+    lib.attn_workspace_bytes.argtypes = [ctypes.POINTER(AttnVariantDesc)]
     lib.attn_status_string.restype = ctypes.c_char_p
     lib.attn_status_string.argtypes = [ctypes.c_int]
     lib.attn_abi_version.restype = ctypes.c_int

@@ -19,6 +19,17 @@
 
 namespace {
 
+// The most key splits of a row tile (attn_combine takes one per lane).
+constexpr int64_t kMaxSplits = 64;
+// Flat query rows (query heads of a kv group x queries) that the decode kernel
+// serves: always up to 64, and up to 128 while there are at most 256 kv groups.
+// Four row tiles beside one workgroup of the prefill kernel: 128 groups of 4
+// heads x 32 queries and 4000 keys 85 against 102 us, 64 groups of 128 queries
+// and 6000 keys 68 against 110, but 512 groups of 100 queries and 300 keys 21
+// against 14. At two row tiles (32 x 8 groups of 8 heads x 8 queries, 1000
+// keys) 28 against 100, at one head of 64 queries 57 against 57.
+constexpr int64_t kDecodeFlatRows = 64, kDecodeFlatRowsFew = 128, kDecodeFewGroups = 256;
+
 bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15u) == 0; }
 
 // Resolve one tensor's strides (0 = contiguous default) and check them.
@@ -144,7 +155,8 @@ void log_plan(const attn_variant_desc& d, const AttnParams& p)
     static const char* norms[] = {"softmax", "relu", "sigmoid"};
     const bool closed = d.mask_kind >= ATTN_MASK_NONE && d.mask_kind <= ATTN_MASK_PREFIX_LM;
     const bool both = p.slopes && p.relpos;
-    const char* path = p.gtok ? "general, listed global set"
+    const char* path = p.decode ? "decode"
+                       : p.gtok ? "general, listed global set"
                        : (d.norm_kind != ATTN_NORM_SOFTMAX || !closed || both) ? "general"
                        : p.band.wl >= 0 ? "closed-form band with a left bound"
                                         : "closed-form band, running max checked through the row sums";
@@ -156,12 +168,12 @@ void log_plan(const attn_variant_desc& d, const AttnParams& p)
     std::fprintf(stderr,
                  "attn_fwd: %s D=%d B=%d Hq=%d Hkv=%d %s mask=%s norm=%s alibi=%d relpos=%d "
                  "softcap=%g (%s) | %s kernel, grid %d, %d rows x %d heads per workgroup, "
-                 "order %s, chunk %d%s, global-row items %d\n",
+                 "order %s, chunk %d%s, global-row items %d, key splits %d\n",
                  d.dtype == ATTN_BF16 ? "bf16" : "fp32", d.head_dim, d.batch, d.num_q_heads,
                  d.num_kv_heads, p.cu_q ? "varlen" : "fixed-length", masks[d.mask_kind],
                  norms[d.norm_kind], p.slopes != nullptr, p.relpos, (double)d.softcap, cap,
                  d.dtype == ATTN_BF16 ? path : "fp32", p.grid, p.wg_rows, p.hp, order, p.chunk,
-                 p.compact ? ", packed grid" : "", p.glob_items);
+                 p.compact ? ", packed grid" : "", p.glob_items, p.splits);
 }
 
 }  // namespace
@@ -294,12 +306,18 @@ extern "C" int attn_row_range(const attn_variant_desc* desc, const int32_t* segm
     return ATTN_OK;
 }
 
-extern "C" int attn_fwd(const void* q, const void* k, const void* v, void* out, float* lse,
-                        const attn_variant_desc* desc)
+namespace {
+
+// Sizes of a call derived from its descriptor.
+struct CallShape {
+    int64_t max_q, max_k;   // longest query and key length
+    int64_t q_tiles, blocks;
+    int hp, block_m;
+};
+
+// Check everything but the pointers and resolve the strides (p.s*_*).
+int check_shape(const attn_variant_desc& d, AttnParams& p, CallShape* c)
 {
-    if (!desc) return ATTN_ERR_NULL_PTR;
-    if (desc->struct_size != sizeof(attn_variant_desc)) return ATTN_ERR_ABI;
-    const attn_variant_desc& d = *desc;
     if (d.dtype != ATTN_BF16 && d.dtype != ATTN_FP32) return ATTN_ERR_UNSUPPORTED;
     if (d.head_dim != 64 && d.head_dim != 128) return ATTN_ERR_UNSUPPORTED;
     if (d.batch < 0 || d.num_q_heads <= 0 || d.num_kv_heads <= 0) return ATTN_ERR_BAD_SHAPE;
@@ -324,7 +342,6 @@ extern "C" int attn_fwd(const void* q, const void* k, const void* v, void* out, 
     const int64_t elt = d.dtype == ATTN_BF16 ? 2 : 4;
     const int64_t align = 16 / elt;
     const int64_t D = d.head_dim;
-    AttnParams p = {};
     rc = resolve_strides(varlen, d.num_q_heads, max_q, D, align, d.stride_q_b, d.stride_q_h,
                          d.stride_q_s, &p.sq_b, &p.sq_h, &p.sq_s);
     if (rc == ATTN_OK)
@@ -364,15 +381,31 @@ extern "C" int attn_fwd(const void* q, const void* k, const void* v, void* out, 
     // together (their K/V reads then meet in the L2)
     const int64_t q_tiles = (max_q + hp * block_m - 1) / (hp * block_m) * hp;
     const int64_t blocks = q_tiles * (d.num_q_heads / hp) * (int64_t)d.batch;
-    if (blocks > INT32_MAX) return ATTN_ERR_UNSUPPORTED;
-    if (blocks == 0) return ATTN_OK;  // nothing to compute
+    // (the fp32 kernel numbers its workgroups with 32 unsigned bits)
+    if (blocks > (d.dtype == ATTN_BF16 ? (int64_t)INT32_MAX : (int64_t)UINT32_MAX))
+        return ATTN_ERR_UNSUPPORTED;
+    if (blocks > 0 && (int64_t)d.batch * d.num_q_heads > INT32_MAX) return ATTN_ERR_UNSUPPORTED;
+    c->max_q = max_q;
+    c->max_k = max_k;
+    c->q_tiles = q_tiles;
+    c->blocks = blocks;
+    c->hp = hp;
+    c->block_m = block_m;
+    return ATTN_OK;
+}
 
+// The pointer checks of a call that has something to compute.
+int check_pointers(const attn_variant_desc& d, const AttnParams& p, const CallShape& c, const void* q,
+                   const void* k, const void* v, const void* out, const float* lse)
+{
+    const int64_t D = d.head_dim;
+    const int varlen = d.cu_seqlens_q != nullptr;
     if (!q || !k || !v || !out) return ATTN_ERR_NULL_PTR;
     if (segment_mask(d.mask_kind) && !d.segment_starts) return ATTN_ERR_NULL_PTR;
     {
         // output rows must not overlap (inputs may: a broadcast K/V is fine)
         const int64_t osize[3] = {varlen ? d.total_q : (int64_t)d.batch, d.num_q_heads,
-                                  varlen ? 1 : max_q};
+                                  varlen ? 1 : c.max_q};
         const int64_t ostride[3] = {varlen ? p.so_s : p.so_b, p.so_h, p.so_s};
         if (!rows_disjoint(D, 3, osize, ostride)) return ATTN_ERR_BAD_SHAPE;
     }
@@ -380,11 +413,57 @@ extern "C" int attn_fwd(const void* q, const void* k, const void* v, void* out, 
         return ATTN_ERR_ALIGNMENT;
     if ((reinterpret_cast<uintptr_t>(lse) & 3u) != 0) return ATTN_ERR_ALIGNMENT;
 
-    p.q = q;
-    p.k = k;
-    p.v = v;
-    p.o = out;
-    p.lse = lse;
+    return ATTN_OK;
+}
+
+// Key tiles of `bn` keys that a row tile spanning `span` query positions can
+// touch, at most.
+int64_t max_key_tiles(const AttnParams& p, int64_t max_k, int64_t span, int64_t bn)
+{
+    int64_t keys = max_k;
+    if (p.band.wl >= 0 && p.band.wr >= 0) {
+        const int64_t seen = (int64_t)p.band.wl + p.band.wr + span;
+        if (seen < keys) return seen / bn + 2;  // a run of keys that starts anywhere in a tile
+    }
+    return (keys + bn - 1) / bn;
+}
+
+// Key splits of the decode kernel for `units` row tiles of max_tiles key tiles
+// at most and avg_tiles on average. A split and its combining launch cost about
+// 2.5 us, so up to 512 keys stay whole (300 keys: 6.7 us whole, 9.0 split).
+// Beyond, a split takes at least an eighth of the tiles, up to 512 keys (1000
+// keys, one sequence: 9.4 us in eight splits, 11.6 in two; 8192 keys: 13.7 us
+// in splits of 512, 14.4 of 256, 16.1 of 1024). Sequences of one length share
+// the chip evenly when there is one workgroup per CU (32 sequences of 1024
+// keys, 8 kv heads: 24.8 us whole, 29.5 in two splits); packed ones of uneven
+// length are cut into eight times as many pieces, so that the longest do not
+// outlast the rest (32 of 256..8192 keys: 138 us with 256 pieces aimed at, 119
+// with 1024, 116 with 2048).
+void split_decode(AttnParams& p, bool packed, int64_t units, int64_t max_tiles, int64_t avg_tiles)
+{
+    if (max_tiles <= 16) return;
+    const int64_t pieces = packed ? 2048 : 256;
+    if (avg_tiles > max_tiles) avg_tiles = max_tiles;
+    int64_t per = (units * avg_tiles + pieces - 1) / pieces;
+    int64_t least = max_tiles / 8 < 16 ? max_tiles / 8 : 16;
+    const int64_t floor_splits = (max_tiles + kMaxSplits - 1) / kMaxSplits;
+    if (least < floor_splits) least = floor_splits;
+    if (per < least) per = least;
+    per = (per + 3) / 4 * 4;  // whole rounds of the four waves
+    const int64_t splits = (max_tiles + per - 1) / per;
+    if (splits <= 1) return;
+    p.splits = (int32_t)splits;
+    p.split_tiles = (int32_t)per;
+}
+
+// Everything the kernels take but the data pointers: schedule and score
+// constants. Needs check_shape's results.
+int plan_launch(const attn_variant_desc& d, AttnParams& p, const CallShape& c)
+{
+    const int varlen = d.cu_seqlens_q != nullptr;
+    const int64_t D = d.head_dim, elt = d.dtype == ATTN_BF16 ? 2 : 4;
+    const int64_t max_q = c.max_q, q_tiles = c.q_tiles, blocks = c.blocks;
+    const int hp = c.hp, block_m = c.block_m, group = d.num_q_heads / d.num_kv_heads;
     p.slopes = d.alibi_slopes;
     p.cu_q = d.cu_seqlens_q;
     p.cu_k = d.cu_seqlens_k;
@@ -521,7 +600,7 @@ extern "C" int attn_fwd(const void* q, const void* k, const void* v, void* out, 
     }
     // bf16 variable-length batch walked one kv group at a time per XCD: a
     // packed grid of only the query spans each sequence has, when smaller.
-    p.grid = (int32_t)blocks;
+    p.grid = (int32_t)(uint32_t)blocks;
     p.compact = 0;
     p.groups_per_xcd = 0;
     p.items_per_tile = gsets;
@@ -543,14 +622,96 @@ extern "C" int attn_fwd(const void* q, const void* k, const void* v, void* out, 
         p.glob_items = (int32_t)items;
         p.grid += p.glob_items;
     }
+    p.decode = 0;
+    p.splits = 1;
+    p.split_tiles = 1 << 30;
+    p.ws_rows = varlen ? (int64_t)d.num_q_heads * d.total_q
+                       : (int64_t)d.batch * d.num_q_heads * d.seqlen_q;
+    // Few query rows per kv head: the decode kernel (schedule overrides keep
+    // the prefill kernel that they describe).
+    const int64_t groups = (int64_t)d.batch * d.num_kv_heads;
+    const int64_t flat = max_q * group, rt = (flat + attn::decode_rows() - 1) / attn::decode_rows();
+    const bool scheduled = d.sched_heads_per_wg || d.sched_order || d.sched_chunk;
+    if (d.dtype == ATTN_BF16 && d.norm_kind == ATTN_NORM_SOFTMAX && closed_form_mask(d.mask_kind) &&
+        !scheduled && groups * rt <= (1 << 20) &&
+        flat <= (groups <= kDecodeFewGroups ? kDecodeFlatRowsFew : kDecodeFlatRows)) {
+        p.decode = 1;
+        p.num_q_tiles = (int32_t)rt;
+        p.div_group = make_fastdiv((uint32_t)group);
+        const int64_t bn = attn::decode_keys();
+        const int64_t avg_k = varlen ? d.total_k / d.batch : d.seqlen_k;
+        split_decode(p, varlen, groups * rt, max_key_tiles(p, c.max_k, max_q, bn),
+                     (avg_k + bn - 1) / bn);
+        p.grid = (int32_t)(groups * rt * p.splits);
+    }
+    return ATTN_OK;
+}
+
+int64_t workspace_need(const AttnParams& p, int64_t D)
+{
+    return p.splits > 1 ? p.splits * p.ws_rows * (D + 4) * 4 : 0;
+}
+
+}  // namespace
+
+extern "C" int64_t attn_workspace_bytes(const attn_variant_desc* desc)
+{
+    if (!desc) return ATTN_ERR_NULL_PTR;
+    if (desc->struct_size != sizeof(attn_variant_desc)) return ATTN_ERR_ABI;
+    AttnParams p = {};
+    CallShape c;
+    int rc = check_shape(*desc, p, &c);
+    if (rc == ATTN_OK && c.blocks == 0) return 0;
+    if (rc == ATTN_OK) rc = plan_launch(*desc, p, c);
+    return rc == ATTN_OK ? workspace_need(p, desc->head_dim) : rc;
+}
+
+extern "C" int attn_fwd(const void* q, const void* k, const void* v, void* out, float* lse,
+                        const attn_variant_desc* desc)
+{
+    return attn_fwd_ws(q, k, v, out, lse, desc, nullptr, 0);
+}
+
+extern "C" int attn_fwd_ws(const void* q, const void* k, const void* v, void* out, float* lse,
+                           const attn_variant_desc* desc, void* workspace, int64_t workspace_bytes)
+{
+    if (!desc) return ATTN_ERR_NULL_PTR;
+    if (desc->struct_size != sizeof(attn_variant_desc)) return ATTN_ERR_ABI;
+    const attn_variant_desc& d = *desc;
+    AttnParams p = {};
+    CallShape c;
+    int rc = check_shape(d, p, &c);
+    if (rc != ATTN_OK) return rc;
+    if (c.blocks == 0) return ATTN_OK;  // nothing to compute
+    rc = check_pointers(d, p, c, q, k, v, out, lse);
+    if (rc == ATTN_OK && !aligned16(workspace)) rc = ATTN_ERR_ALIGNMENT;
+    if (rc == ATTN_OK) rc = plan_launch(d, p, c);
+    if (rc != ATTN_OK) return rc;
+    p.q = q;
+    p.k = k;
+    p.v = v;
+    p.o = out;
+    p.lse = lse;
+    const int64_t need = workspace_need(p, d.head_dim);
+    if (need > 0 && (!workspace || workspace_bytes < need)) {  // one workgroup per row tile
+        p.grid /= p.splits;
+        p.splits = 1;
+        p.split_tiles = 1 << 30;
+    } else if (need > 0) {
+        p.ws_o = static_cast<float*>(workspace);
+        p.ws_ml = p.ws_o + p.splits * p.ws_rows * d.head_dim;
+    }
     if (d.flags & ATTN_FLAG_VALIDATE) {
-        rc = validate_device_inputs(d, varlen, segment_mask(d.mask_kind), glist);
+        rc = validate_device_inputs(d, p.cu_q != nullptr, p.seg != nullptr, p.gtok != nullptr);
         if (rc != ATTN_OK) return rc;
     }
     hipStream_t stream = static_cast<hipStream_t>(d.stream);
     if (d.flags & ATTN_FLAG_LOG) log_plan(d, p);
-    hipError_t err = d.dtype == ATTN_BF16 ? attn::launch_bf16(p, d.head_dim, stream)
-                                          : attn::launch_f32(p, d.head_dim, stream);
+    hipError_t err = p.decode                ? attn::launch_bf16_decode(p, d.head_dim, stream)
+                     : d.dtype == ATTN_BF16 ? attn::launch_bf16(p, d.head_dim, stream)
+                                            : attn::launch_f32(p, d.head_dim, stream);
+    if (err == hipSuccess && p.splits > 1)
+        err = attn::launch_combine(p, d.head_dim, d.dtype == ATTN_BF16, stream);
     if (err != hipSuccess && (d.flags & ATTN_FLAG_LOG))
         std::fprintf(stderr, "attn_fwd: launch failed: %s\n", hipGetErrorString(err));
     return err == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;

@@ -1,0 +1,123 @@
+// attn_combine.hip -- add up the partial results of query rows whose keys were
+// split over workgroups (Eq. 1 restated over key ranges): with m the largest
+// running max of a row's partials and w_s = 2^(m_s - m),
+//   O = sum w_s O_s / sum w_s lo_s,  LSE = (m + log2 sum w_s l_s) ln 2,
+// l the fp32 row sum and lo the sum that normalises O (ReLU and Sigmoid: O =
+// sum O_s). A partial without keys has m = -inf and l = 0; a row that was not
+// split has lo = -1 in its first partial, and its output is written. One wavefront per row:
+// it takes the rows' scalars one split per lane, then walks the splits' O in
+// 16-byte pieces, D / 4 lanes side by side. Bound by the latency of its loads:
+// 16 splits are in flight at a time.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kernel_params.h"
+#include "launch.h"
+#include "score_mods.h"
+
+namespace attn {
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+constexpr int NT = 256;
+
+template <int D, class OUT>
+__global__ __launch_bounds__(NT) void attn_combine_kernel(AttnParams p)
+{
+    constexpr int COLS = D / 4, PAR = 64 / COLS;  // pieces of a row, splits side by side
+    constexpr int BATCH = 16 / PAR;               // loads in flight per lane
+    const int lane = threadIdx.x & 63;
+    const int64_t row = (int64_t)blockIdx.x * (NT / 64) + (threadIdx.x >> 6);
+    if (row >= p.ws_rows) return;
+    const bool varlen = p.cu_q != nullptr;
+    const int64_t per_head = varlen ? p.total_q : p.seqlen_q;
+    const int64_t bh = row / per_head, i = row - bh * per_head;
+    if (varlen && i >= p.cu_q[p.batch]) return;  // a token of no sequence: nothing was computed
+    const int64_t b = varlen ? 0 : bh / p.hq, h = bh - b * p.hq;
+
+    // The O pieces of the first BATCH splits are requested beside the scalars
+    // that weight them, so a row of few splits waits for memory once (a split
+    // that saw no key of the row wrote no O: what is read there is not used).
+    const int col = lane % COLS, par = lane / COLS;
+    const float* src = p.ws_o + row * D + 4 * col;
+    f32x4 x[BATCH];
+    auto load = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int s = min(s0 + u * PAR + par, p.splits - 1);
+            x[u] = *reinterpret_cast<const f32x4*>(src + s * p.ws_rows * D);
+        }
+    };
+    // one split per lane (the launcher keeps them within a wavefront)
+    const f32x4 sc = *reinterpret_cast<const f32x4*>(
+        p.ws_ml + (min(lane, p.splits - 1) * p.ws_rows + row) * 4);
+    load(0);
+    const bool have = lane < p.splits;
+    const float m = have ? sc[0] : -__builtin_inff(), shift = sc[3];
+    float l = have ? sc[1] : 0.0f, lo = have ? sc[2] : 0.0f;
+    if (__shfl(lo, 0) < 0.0f) return;  // the row was not split and is written
+    float m_tot = m;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) m_tot = __builtin_fmaxf(m_tot, __shfl_xor(m_tot, d));
+    // (m = -inf with a NaN sum: every score was NaN, which must reach the output)
+    const float w = m == -__builtin_inff() && l == 0.0f ? 0.0f : __builtin_amdgcn_exp2f(m - m_tot);
+    l *= w;
+    lo *= w;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        l += __shfl_xor(l, d);
+        lo += __shfl_xor(lo, d);
+    }
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int s0 = 0; s0 < p.splits; s0 += BATCH * PAR) {
+        if (s0 > 0) load(s0);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int s = s0 + u * PAR + par;
+            const float ws = __shfl(w, s & 63);
+            if (s < p.splits && ws != 0.0f) acc += x[u] * ws;
+        }
+    }
+#pragma unroll
+    for (int d = COLS; d < 64; d <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], d);
+    if (par == 0) {
+        // ReLU, Sigmoid: the partials are shares of O (weight 1 each)
+        const float inv = p.norm != kNormSoftmax ? 1.0f
+                          : l > 0.0f && lo > 0.0f ? 1.0f / lo
+                                                  : l != l ? l : 0.0f;
+        OUT* dst = static_cast<OUT*>(p.o) + b * p.so_b + h * p.so_h + i * p.so_s + 4 * col;
+        acc *= inv;
+        if constexpr (sizeof(OUT) == 2) {
+            bf16x4 y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = (__bf16)acc[e];
+            *reinterpret_cast<bf16x4*>(dst) = y;
+        } else {
+            *reinterpret_cast<f32x4*>(dst) = acc;
+        }
+    }
+    if (lane == 0 && p.lse && p.norm == kNormSoftmax)
+        p.lse[row] = l > 0.0f ? (m_tot + __builtin_log2f(l)) * kLn2 + shift : -__builtin_inff();
+}
+
+template <int D, class OUT>
+hipError_t launch(const AttnParams& p, hipStream_t stream)
+{
+    const int64_t blocks = (p.ws_rows + NT / 64 - 1) / (NT / 64);
+    hipLaunchKernelGGL((attn_combine_kernel<D, OUT>), dim3((unsigned)blocks), dim3(NT), 0, stream, p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_combine(const AttnParams& p, int head_dim, bool bf16, hipStream_t stream)
+{
+    if (bf16) return head_dim == 128 ? launch<128, __bf16>(p, stream) : launch<64, __bf16>(p, stream);
+    return head_dim == 128 ? launch<128, float>(p, stream) : launch<64, float>(p, stream);
+}
+
+}  // namespace attn

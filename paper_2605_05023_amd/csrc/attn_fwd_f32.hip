@@ -123,8 +123,9 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_f32_kernel(AttnParams p)
     // round-robin over the 8 XCDs) and read its K/V through one L2.
     int b, hq, qt;
     {
-        const int w = blockIdx.x, nbh = p.batch * p.hq;
-        int t = w / nbh, r = w - t * nbh;
+        const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x, nbh = (uint32_t)(p.batch * p.hq);
+        if (w >= (uint32_t)p.grid) return;
+        const int t = (int)(w / nbh), r = (int)(w - (uint32_t)t * nbh);
         if (p.map_mode == 1) {
             const int x = r & 7, k = r >> 3, gpx = (p.batch * p.hkv) >> 3;
             const int h = k / gpx, g = x + 8 * (k - h * gpx);  // head in group, kv group
@@ -451,9 +452,10 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_f32_kernel(AttnParams p)
 template <int D, bool SOFTCAP, int BIAS, int NORM, bool GEN>
 hipError_t launch(const AttnParams& p, hipStream_t stream)
 {
-    int64_t blocks = (int64_t)p.num_q_tiles * p.hq * p.batch;
-    hipLaunchKernelGGL((attn_fwd_f32_kernel<D, SOFTCAP, BIAS, NORM, GEN>), dim3((unsigned)blocks),
-                       dim3(NT), 0, stream, p);
+    // rows of 2^22 workgroups: a grid dimension holds less than 2^32 threads
+    const uint32_t blocks = (uint32_t)p.grid, gx = blocks < (1u << 22) ? blocks : 1u << 22;
+    hipLaunchKernelGGL((attn_fwd_f32_kernel<D, SOFTCAP, BIAS, NORM, GEN>),
+                       dim3(gx, (blocks - 1) / gx + 1), dim3(NT), 0, stream, p);
     return hipGetLastError();
 }
 

@@ -64,6 +64,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -444,6 +445,28 @@ struct WaveState {
     int lh, pfx, jlo, jhi, ip, jref;
     float bias_abs, bias_lin;  // coefficients of |ip - j| and (jref - j), in units
 };
+
+// LDS read offsets (within a tile) of this lane's K and V fragments.
+template <class T>
+__device__ __forceinline__ void lds_read_offsets(WaveState<T>& ws, int lane)
+{
+    const int li = lane & 31, lh = lane >> 5;
+    const int r = pi32(li);
+#pragma unroll
+    for (int t = 0; t < T::KSTEPS; ++t)
+        ws.kaddr[t] = r * T::ROWB + (((2 * t + lh) ^ chunk_swizzle<T::D>(r)) << 4);
+    const int g = lane >> 4, sl = lane & 15, a = sl & 3, f = sl >> 2;
+    const int sa = ((a & 1) << 1) | (a >> 1);  // head-dim order pi on O^T rows
+#pragma unroll
+    for (int d = 0; d < T::DBLK; ++d)
+#pragma unroll
+        for (int rr = 0; rr < 2; ++rr) {
+            int key = 8 * (g >> 1) + 4 * rr + f;
+            int dd = 32 * d + 16 * (g & 1) + 4 * sa;
+            ws.vaddr[d][rr] = key * T::ROWB + (((dd >> 3) ^ chunk_swizzle<T::D>(key)) << 4) +
+                              (dd & 7) * 2;
+        }
+}
 
 // Visible-key bounds of this lane's row relative to the key of element
 // offset 0 in a tile (jn + 8 lh), so each element compares its compile-time
@@ -1204,24 +1227,7 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_bf16_kernel(AttnParams p)
             ws.qf[t] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(qrs, off, 0, 0));
         }
     }
-    // LDS read offsets (within a tile).
-    {
-        const int r = pi32(li);
-#pragma unroll
-        for (int t = 0; t < T::KSTEPS; ++t)
-            ws.kaddr[t] = r * T::ROWB + (((2 * t + lh) ^ chunk_swizzle<D>(r)) << 4);
-        const int g = lane >> 4, sl = lane & 15, a = sl & 3, f = sl >> 2;
-        const int sa = ((a & 1) << 1) | (a >> 1);  // head-dim order pi on O^T rows
-#pragma unroll
-        for (int d = 0; d < T::DBLK; ++d)
-#pragma unroll
-            for (int rr = 0; rr < 2; ++rr) {
-                int key = 8 * (g >> 1) + 4 * rr + f;
-                int dd = 32 * d + 16 * (g & 1) + 4 * sa;
-                ws.vaddr[d][rr] = key * T::ROWB + (((dd >> 3) ^ chunk_swizzle<D>(key)) << 4) +
-                                  (dd & 7) * 2;
-            }
-    }
+    lds_read_offsets<T>(ws, lane);
 
     const uint32_t klp = load_lane_offset<T>(wave, lane, p.sk_s);
     const uint32_t vlp = load_lane_offset<T>(wave, lane, p.sv_s);

@@ -45,7 +45,7 @@ struct AttnParams {
     int32_t compact;
     int32_t groups_per_xcd;  // batch * hkv / 8
     int32_t items_per_tile;  // workgroups per query tile of a kv group: group / hp
-    int32_t grid;            // bf16: workgroups launched
+    int32_t grid;            // workgroups launched (fp32: 32 unsigned bits)
     // bf16 listed global set: the first glob_items workgroups compute the rows
     // of G, wg_rows list entries each (glob_chunks per sequence and head set)
     int32_t glob_items, glob_chunks;
@@ -94,4 +94,14 @@ struct AttnParams {
     // dot * sum_k cap_poly[k] dot^(2k) while dot^2 <= cap_zmax.
     float cap_poly[3];
     float cap_zmax;
+    // Key splits: `splits` workgroups share the key tiles of one row tile,
+    // split_tiles consecutive ones each, and leave partial results in the
+    // caller's workspace for attn_combine: ws_o [splits][ws_rows][D] and ws_ml
+    // [splits][ws_rows][4] (running max, fp32 row sum, the sum that normalises
+    // O, LSE shift), rows indexed as the LSE. splits = 1: no workspace.
+    int32_t decode;          // bf16 decode kernel (num_q_tiles: its row tiles)
+    int32_t splits, split_tiles;
+    int64_t ws_rows;
+    float* ws_o;
+    float* ws_ml;
 };

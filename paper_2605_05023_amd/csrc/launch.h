@@ -22,6 +22,14 @@ hipError_t launch_bf16_glist_softmax(const AttnParams& p, int head_dim, hipStrea
 hipError_t launch_bf16_glist_relu(const AttnParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_bf16_glist_sigmoid(const AttnParams& p, int head_dim, hipStream_t stream);
 
+// few query rows per kv head (softmax, closed-form masks): flat rows per
+// workgroup and keys per tile of the decode kernel, and its launch
+int decode_rows();
+int decode_keys();
+hipError_t launch_bf16_decode(const AttnParams& p, int head_dim, hipStream_t stream);
+// add up the partial results of a launch with p.splits > 1
+hipError_t launch_combine(const AttnParams& p, int head_dim, bool bf16, hipStream_t stream);
+
 // fp32 inputs and arithmetic; head_dim 64 or 128.
 hipError_t launch_f32(const AttnParams& p, int head_dim, hipStream_t stream);
 int f32_block_m();

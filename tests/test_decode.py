@@ -1,0 +1,192 @@
+"""The decode kernel (few query rows per kv head) and its key splits.
+
+The row tile holds 32 flat rows (query heads of a kv group x queries), the
+waves take every fourth 32-key tile, and longer key ranges are split over
+workgroups when a workspace is given, so the cases sit around 32 flat rows,
+32 and 128 keys, and one and several splits with a ragged last one. Each runs
+with the workspace that `fwd` allocates and without one (attn_fwd); both are
+compared with the fp64 oracle element by element at the bars of the other
+parity tests, and with each other at twice the rounding of bf16 outputs.
+"""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_05023_amd as attn
+from gpu_util import LSE_TOL, O_TOL, gpu_available, log
+from paper_2605_05023_amd import _abi
+from paper_2605_05023_amd.build import LIB_POISON
+from paper_2605_05023_amd.workloads import (MASK_CAUSAL, MASK_NAMES, MASK_NONE, MASK_PREFIX_LM,
+                                            MASK_SLIDING_WINDOW, alibi_slopes)
+
+# (D, group, hkv, [(lq, lk)] (packed when they differ), mask, options)
+CASES = [
+    (128, 1, 1, [(1, 1)], MASK_NONE, {}),
+    (64, 8, 2, [(1, 31)] * 2, MASK_CAUSAL, {}),
+    (128, 31, 1, [(1, 129)], MASK_CAUSAL, dict(alibi=True)),
+    (64, 32, 1, [(1, 513)], MASK_CAUSAL, dict(softcap=30.0)),
+    (128, 33, 1, [(1, 545)], MASK_CAUSAL, dict(relpos=True)),
+    (128, 3, 2, [(21, 700)] * 2, MASK_CAUSAL, {}),
+    (64, 4, 2, [(32, 33)], MASK_CAUSAL, {}),
+    (128, 1, 8, [(128, 1100)], MASK_CAUSAL, {}),
+    (128, 4, 2, [(5, 3)], MASK_CAUSAL, {}),  # rows that see no key
+    (128, 4, 2, [(2, 2000)] * 3, MASK_SLIDING_WINDOW, dict(window=(700, 3))),
+    (64, 4, 2, [(3, 1500)], MASK_SLIDING_WINDOW, dict(window=(40, 0), softcap=400.0)),
+    (128, 16, 1, [(2, 4001)], MASK_PREFIX_LM, dict(prefix_len=3999, alibi=True, relpos=True,
+                                                   softcap=50.0)),
+    (128, 4, 2, [(1, 1), (4, 3000), (0, 50), (2, 0), (3, 700), (1, 512), (0, 0)], MASK_CAUSAL, {}),
+    (64, 2, 4, [(1, 600), (1, 5), (1, 2500), (1, 64)], MASK_NONE, dict(alibi=True)),
+]
+
+
+def _inputs(c):
+    D, group, hkv, lens, mask, opt = c
+    g = torch.Generator().manual_seed(sum(a * 31 + b for a, b in lens) + D + group)
+    packed = len(set(lens)) > 1
+    lq, lk = [a for a, _ in lens], [b for _, b in lens]
+    hq = hkv * group
+    qs = (sum(lq), hq, D) if packed else (len(lens), hq, lq[0], D)
+    ks = (sum(lk), hkv, D) if packed else (len(lens), hkv, lk[0], D)
+    q, k, v = (torch.randn(s, generator=g).to(torch.bfloat16) for s in (qs, ks, ks))
+    kw = dict(mask=MASK_NAMES[mask], softcap=opt.get("softcap", 0.0),
+              relative_position=opt.get("relpos", False), prefix_len=opt.get("prefix_len", 0))
+    okw = dict(mask=mask, softcap=opt.get("softcap", 0.0), relpos=opt.get("relpos", False),
+               prefix_len=opt.get("prefix_len", 0))
+    if "window" in opt:
+        kw["window"] = opt["window"]
+        okw.update(window_left=opt["window"][0], window_right=opt["window"][1])
+    if opt.get("alibi"):
+        kw["alibi_slopes"] = alibi_slopes(hq).cuda()
+        okw["slopes"] = alibi_slopes(hq)
+    if packed:
+        cuq, cuk = (torch.tensor([0] + list(np.cumsum(x)), dtype=torch.int32) for x in (lq, lk))
+        kw.update(cu_seqlens_q=cuq.cuda(), cu_seqlens_k=cuk.cuda(), max_seqlen_q=max(lq),
+                  max_seqlen_k=max(lk))
+        okw.update(cu_seqlens_q=cuq, cu_seqlens_k=cuk)
+    return q, k, v, packed, kw, okw
+
+
+def _call(lib, q, k, v, packed, kw, workspace):
+    out = torch.empty_like(q)
+    lse = torch.empty(attn.lse_shape(q, packed), dtype=torch.float32, device=q.device)
+    d = attn.make_desc(q, k, v, out, **kw)
+    n = lib.attn_workspace_bytes(ctypes.byref(d)) if workspace else 0
+    ws = torch.full((max(n, 16),), 255, dtype=torch.uint8, device=q.device)  # NaN
+    st = lib.attn_fwd_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
+                         ctypes.byref(d), ws.data_ptr() if n else None, n)
+    assert st == 0
+    return out, lse
+
+
+def _check(o, lse, o_ref, lse_ref, what):
+    og = o.float().cpu().numpy().astype(np.float64)
+    lg = lse.cpu().numpy().astype(np.float64)
+    assert np.isfinite(og).all()
+    assert np.array_equal(np.isinf(lg), np.isinf(lse_ref)), what
+    fin = np.isfinite(lse_ref)
+    o_err = float(np.abs(og - o_ref).max()) if og.size else 0.0
+    l_err = float(np.abs(lg[fin] - lse_ref[fin]).max()) if fin.any() else 0.0
+    log(f"  {what}: max|dO| = {o_err:.3e}, max|dLSE| = {l_err:.3e}")
+    assert o_err <= O_TOL["bf16"] and l_err <= LSE_TOL, what
+
+
+@pytest.mark.parametrize("i", range(len(CASES)))
+@pytest.mark.gpu
+@pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
+def test_decode_parity(i):
+    c = CASES[i]
+    log(f"[decode] {c}")
+    q, k, v, packed, kw, okw = _inputs(c)
+    qg, kg, vg = q.cuda(), k.cuda(), v.cuda()
+    o, lse = attn.fwd(qg, kg, vg, **kw)
+    o1, lse1 = _call(attn.load(), qg, kg, vg, packed, kw, False)
+    torch.cuda.synchronize()
+    o_ref, lse_ref = oracle.attention(q, k, v, scale=c[0] ** -0.5, **okw)
+    _check(o, lse, o_ref, lse_ref, "with workspace")
+    _check(o1, lse1, o_ref, lse_ref, "without")
+    # P is rounded against another running max: two roundings of 2^-8 each
+    scale = max(1.0, float(np.abs(o_ref).max())) if o_ref.size else 1.0
+    assert float((o.float() - o1.float()).abs().max()) <= 2 * 2 ** -8 * scale
+
+
+@pytest.mark.parametrize("i", [0, 5, 9, 12, 13])
+@pytest.mark.gpu
+@pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
+def test_poisoned_lds_and_workspace_change_nothing(i):
+    q, k, v, packed, kw, _ = _inputs(CASES[i])
+    a = (q.cuda(), k.cuda(), v.cuda(), packed, kw, True)
+    o, lse = _call(attn.load(), *a)
+    o1, lse1 = _call(_abi.load(LIB_POISON), *a)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o.float()).all()
+    assert torch.equal(o, o1) and torch.equal(lse, lse1)
+
+
+@pytest.mark.gpu
+@pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
+def test_nan_query_row_stays_nan():
+    """A NaN query gives NaN outputs for its row alone, split or not."""
+    g = torch.Generator().manual_seed(1)
+    q = torch.randn(1, 4, 2, 128, generator=g).to(torch.bfloat16)
+    q[0, 1, 0, 5] = float("nan")
+    k, v = (torch.randn(1, 1, 3000, 128, generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    o, _ = attn.fwd(q.cuda(), k, v, causal=True)
+    torch.cuda.synchronize()
+    nan = torch.isnan(o.float()).cpu()
+    assert nan[0, 1, 0].all() and int(nan.sum()) == 128
+
+
+@pytest.mark.gpu
+@pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
+def test_split_call_in_a_graph():
+    """A captured split call gives the eager result on every replay."""
+    g = torch.Generator().manual_seed(2)
+    q = torch.randn(1, 32, 1, 128, generator=g).to(torch.bfloat16).cuda()
+    k, v = (torch.randn(1, 8, 6000, 128, generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    want, want_lse = attn.fwd(q, k, v)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        o, lse = attn.fwd(q, k, v)
+    for _ in range(3):
+        o.zero_()
+        graph.replay()
+        attn.fwd(q[:, :8].contiguous(), k[:, :2].contiguous(), v[:, :2].contiguous())
+        torch.cuda.synchronize()
+        assert torch.equal(o, want) and torch.equal(lse, want_lse)
+
+
+# ---- the ABI of the workspace (no GPU: rejected before any HIP call) --------
+
+def _desc(**kw):
+    d = _abi.AttnVariantDesc.new()
+    d.dtype, d.batch, d.num_q_heads, d.num_kv_heads, d.head_dim = _abi.ATTN_BF16, 1, 32, 8, 128
+    d.scale, d.mask_kind, d.seqlen_q, d.seqlen_k = 0.1, _abi.ATTN_MASK_CAUSAL, 1, 8192
+    for k, v in kw.items():
+        setattr(d, k, v)
+    return d
+
+
+def test_workspace_bytes():
+    lib = attn.load()
+    need = lib.attn_workspace_bytes(ctypes.byref(_desc()))
+    assert need > 0 and need % (32 * (128 + 4) * 4) == 0  # splits x rows x (D + 4) floats
+    assert lib.attn_workspace_bytes(ctypes.byref(_desc(seqlen_k=64))) == 0
+    assert lib.attn_workspace_bytes(ctypes.byref(_desc(batch=0))) == 0
+    assert lib.attn_workspace_bytes(None) == _abi.STATUS_CODE["ATTN_ERR_NULL_PTR"]
+    assert lib.attn_workspace_bytes(ctypes.byref(_desc(struct_size=8))) == \
+        _abi.STATUS_CODE["ATTN_ERR_ABI"]
+    assert lib.attn_workspace_bytes(ctypes.byref(_desc(num_kv_heads=5))) == \
+        _abi.STATUS_CODE["ATTN_ERR_BAD_SHAPE"]
+    assert lib.attn_workspace_bytes(ctypes.byref(_desc(sched_order=3))) == \
+        _abi.STATUS_CODE["ATTN_ERR_BAD_VARIANT"]
+
+
+def test_misaligned_workspace_is_refused():
+    lib, P = attn.load(), 0x10000  # dummy device pointers, never dereferenced
+    d = _desc()
+    st = lib.attn_fwd_ws(P, P, P, P, None, ctypes.byref(d), P + 8, 1 << 30)
+    assert st == _abi.STATUS_CODE["ATTN_ERR_ALIGNMENT"]
