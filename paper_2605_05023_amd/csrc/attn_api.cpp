@@ -456,6 +456,37 @@ void split_decode(AttnParams& p, bool packed, int64_t units, int64_t max_tiles, 
     p.split_tiles = (int32_t)per;
 }
 
+// Key splits of the prefill and fp32 kernels for `items` workgroups with rows,
+// max_tiles key tiles at most and avg_tiles on average, for calls whose
+// workgroups do not fill the chip: pieces for one workgroup per CU, at least
+// `least` tiles each. A workgroup alone on its CU takes tile_us per tile, so a
+// split shortens the longest by saved us; against that stand the second launch
+// and the writing and reading of the partial rows (about 2.5 TB/s), and it is
+// made when it saves a third more than it costs. 32 heads of 256 queries and
+// 8192 keys (64 workgroups): 114 us whole, 49 in 4 splits; 8 heads of 512
+// queries, 4096 keys, D = 64: 45 and 20; 16 heads of 2048 causal rows (256
+// workgroups): 37 whole, 50 in splits of 16 tiles. fp32, 8 heads, one query,
+// 4000 keys: 133 and 17.
+void split_underfilled(AttnParams& p, int64_t D, int64_t items, int64_t max_tiles, int64_t avg_tiles,
+                       int64_t rows, int64_t least, double tile_us)
+{
+    if (avg_tiles > max_tiles) avg_tiles = max_tiles;
+    if (avg_tiles < 1) return;
+    int64_t per = (items * avg_tiles + 255) / 256;
+    const int64_t floor_splits = (max_tiles + kMaxSplits - 1) / kMaxSplits;
+    if (per < floor_splits) per = floor_splits;
+    per = (per + least - 1) / least * least;
+    const int64_t splits = (max_tiles + per - 1) / per;
+    if (splits <= 1) return;
+    int64_t usual = avg_tiles / per + 1;  // splits of the usual row
+    if (usual > splits) usual = splits;
+    const double saved = (double)(max_tiles - per) * tile_us;
+    const double cost = 5.0 + (double)(rows * usual) * (double)(D + 4) * 8.0 / 2.5e6;
+    if (saved < 1.33 * cost) return;
+    p.splits = (int32_t)splits;
+    p.split_tiles = (int32_t)per;
+}
+
 // Everything the kernels take but the data pointers: schedule and score
 // constants. Needs check_shape's results.
 int plan_launch(const attn_variant_desc& d, AttnParams& p, const CallShape& c)
@@ -642,7 +673,19 @@ int plan_launch(const attn_variant_desc& d, AttnParams& p, const CallShape& c)
         const int64_t avg_k = varlen ? d.total_k / d.batch : d.seqlen_k;
         split_decode(p, varlen, groups * rt, max_key_tiles(p, c.max_k, max_q, bn),
                      (avg_k + bn - 1) / bn);
-        p.grid = (int32_t)(groups * rt * p.splits);
+        p.grid = (int32_t)(groups * rt);
+    } else if (!scheduled && !p.gtok) {
+        const bool bf16 = d.dtype == ATTN_BF16;
+        const int64_t bn = bf16 ? attn::bf16_block_n() : attn::f32_block_n();
+        const int64_t usual_q = varlen ? d.total_q / d.batch : d.seqlen_q;
+        const int64_t usual_k = varlen ? d.total_k / d.batch : d.seqlen_k;
+        const int64_t items =
+            groups * (group / hp) * ((usual_q + block_m - 1) / block_m);
+        // causal-like masks: the average row sees usual_k - usual_q / 2 keys
+        const int64_t seen = d.mask_kind == ATTN_MASK_NONE ? usual_k : usual_k - usual_q / 2;
+        const double tile_us = (D == 128 ? 0.85 : 0.5) * (bf16 ? 1.0 : 1.2);
+        split_underfilled(p, D, items, max_key_tiles(p, c.max_k, block_m, bn), (seen + bn - 1) / bn,
+                          p.ws_rows, bf16 ? 8 : 4, tile_us);
     }
     return ATTN_OK;
 }
@@ -694,7 +737,6 @@ extern "C" int attn_fwd_ws(const void* q, const void* k, const void* v, void* ou
     p.lse = lse;
     const int64_t need = workspace_need(p, d.head_dim);
     if (need > 0 && (!workspace || workspace_bytes < need)) {  // one workgroup per row tile
-        p.grid /= p.splits;
         p.splits = 1;
         p.split_tiles = 1 << 30;
     } else if (need > 0) {

@@ -8,6 +8,7 @@
 namespace attn {
 
 int bf16_block_m() { return BM; }
+int bf16_block_n() { return key_tile_width(0); }
 
 namespace {
 

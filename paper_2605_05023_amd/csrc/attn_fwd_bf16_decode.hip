@@ -11,7 +11,7 @@
 //    several times).
 //  * The keys of one row tile are split over the four wavefronts of a
 //    workgroup (every fourth 32-key tile each) and over workgroups (split_tiles
-//    tiles each, the grid's slowest axis), so that a few sequences still fill
+//    tiles each, the grid's second axis), so that a few sequences still fill
 //    the chip. The waves are merged through LDS; the workgroups leave partial
 //    results (running max, row sums and O) in the caller's workspace and
 //    attn_combine (attn_combine.hip) adds them up. Without a workspace a row
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
     // XCD (ids are dealt round-robin over the 8 XCDs), so that they read its K
     // and V at the same time through one L2.
     const uint32_t ngroups = (uint32_t)(p.batch * p.hkv), nrt = (uint32_t)p.num_q_tiles;
-    const uint32_t sp = blockIdx.x / (ngroups * nrt), id = blockIdx.x - sp * (ngroups * nrt);
+    const uint32_t sp = blockIdx.y, id = blockIdx.x;
     uint32_t g, rt;
     if (ngroups % 8 == 0) {
         const uint32_t k = id >> 3;
@@ -298,8 +298,8 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
 template <int D, int CAP, int BIAS>
 hipError_t launch(const AttnParams& p, hipStream_t stream)
 {
-    hipLaunchKernelGGL((attn_decode_bf16_kernel<D, CAP, BIAS>), dim3((unsigned)p.grid), dim3(NT), 0,
-                       stream, p);
+    hipLaunchKernelGGL((attn_decode_bf16_kernel<D, CAP, BIAS>), dim3((unsigned)p.grid, (unsigned)p.splits), dim3(NT),
+                       0, stream, p);
     return hipGetLastError();
 }
 

@@ -122,6 +122,7 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_f32_kernel(AttnParams p)
     // map_mode 1 the query heads of a kv group go to one XCD (ids are dealt
     // round-robin over the 8 XCDs) and read its K/V through one L2.
     int b, hq, qt;
+    const uint32_t sp = blockIdx.z;  // key split
     {
         const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x, nbh = (uint32_t)(p.batch * p.hq);
         if (w >= (uint32_t)p.grid) return;
@@ -198,6 +199,22 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_f32_kernel(AttnParams p)
         gp = plan_tiles(p.band, q0, BM, lq, lk, BN);
         t_lo = gp.lo;
         t_hi = gp.hi;
+    }
+    // This split's share of the tiles. A row tile with no more key tiles than
+    // one split takes is written by its first split as if it were not split.
+    const int64_t row = p.cu_q ? (int64_t)hq * p.total_q + qrow0 + qi
+                               : ((int64_t)b * p.hq + hq) * lq + qi;  // index of its LSE
+    bool partial = false;
+    if (p.splits > 1) {
+        partial = t_hi - t_lo > p.split_tiles;
+        t_lo += (int)sp * p.split_tiles;
+        if ((int)sp < p.splits - 1) t_hi = min(t_hi, t_lo + p.split_tiles);
+        if (sp > 0 && t_lo >= t_hi) {  // no tiles: an empty partial
+            if (wave == 0 && lh == 0 && qi < lq)
+                *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.ws_rows + row) * 4) =
+                    f32x4{-__builtin_inff(), 0.0f, 0.0f, 0.0f};
+            return;
+        }
     }
     auto full_tile = [&](int kt) __attribute__((always_inline)) -> bool {
         if constexpr (GEN) {
@@ -431,21 +448,30 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_f32_kernel(AttnParams p)
     else
         inv = lk > 0 ? 1.0f / (float)lk : 0.0f;
     float* dst = ob + ooff + (int64_t)qi * p.so_s + DB * (8 * wave + 4 * lh);
+    if (partial) {  // unnormalised O (ReLU, Sigmoid: the share of O)
+        dst = p.ws_o + (sp * p.ws_rows + row) * D + DB * (8 * wave + 4 * lh);
+        if (SOFTMAX) inv = 1.0f;
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {  // register 4 wave + e: row 8 wave + 4 lh + e of each block
         const int r = 4 * wave + e;
         const vrow_t x = (part[r * 64] + part[(16 + r) * 64]) + (part[(32 + r) * 64] + part[(48 + r) * 64]);
         *reinterpret_cast<vrow_t*>(dst + DB * e) = x * inv;
     }
-    if (SOFTMAX && p.lse && wave == 0 && lh == 0) {
+    if (p.splits > 1 && wave == 0 && lh == 0) {
+        f32x4 sc = {0.0f, 0.0f, -1.0f, 0.0f};  // written here: nothing to combine
+        if (partial)
+            sc = SOFTMAX ? f32x4{m_tot, l_tot, l_tot, bias_lin != 0.0f ? (float)(ip - jref) : 0.0f}
+                         : f32x4{0.0f, 1.0f, 1.0f, 0.0f};
+        *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.ws_rows + row) * 4) = sc;
+    }
+    if (SOFTMAX && !partial && p.lse && wave == 0 && lh == 0) {
         float lse = -__builtin_inff();
         if (l_tot > 0.0f) {
             lse = (m_tot + __builtin_log2f(l_tot)) * kLn2;
             if (bias_lin != 0.0f) lse += (float)(ip - jref);
         }
-        int64_t idx = p.cu_q ? (int64_t)hq * p.total_q + qrow0 + qi
-                             : ((int64_t)b * p.hq + hq) * lq + qi;
-        p.lse[idx] = lse;
+        p.lse[row] = lse;
     }
 }
 
@@ -455,7 +481,7 @@ hipError_t launch(const AttnParams& p, hipStream_t stream)
     // rows of 2^22 workgroups: a grid dimension holds less than 2^32 threads
     const uint32_t blocks = (uint32_t)p.grid, gx = blocks < (1u << 22) ? blocks : 1u << 22;
     hipLaunchKernelGGL((attn_fwd_f32_kernel<D, SOFTCAP, BIAS, NORM, GEN>),
-                       dim3(gx, (blocks - 1) / gx + 1), dim3(NT), 0, stream, p);
+                       dim3(gx, (blocks - 1) / gx + 1, (unsigned)p.splits), dim3(NT), 0, stream, p);
     return hipGetLastError();
 }
 
@@ -483,6 +509,7 @@ hipError_t launch_d(const AttnParams& p, hipStream_t stream)
 }  // namespace
 
 int f32_block_m() { return BM; }
+int f32_block_n() { return BN; }
 
 hipError_t launch_f32(const AttnParams& p, int head_dim, hipStream_t stream)
 {

@@ -45,7 +45,7 @@ struct AttnParams {
     int32_t compact;
     int32_t groups_per_xcd;  // batch * hkv / 8
     int32_t items_per_tile;  // workgroups per query tile of a kv group: group / hp
-    int32_t grid;            // workgroups launched (fp32: 32 unsigned bits)
+    int32_t grid;            // workgroups of each key split (fp32: 32 unsigned bits)
     // bf16 listed global set: the first glob_items workgroups compute the rows
     // of G, wg_rows list entries each (glob_chunks per sequence and head set)
     int32_t glob_items, glob_chunks;

@@ -11,6 +11,7 @@ namespace attn {
 hipError_t launch_bf16(const AttnParams& p, int head_dim, hipStream_t stream);
 // (query head, query row) pairs per workgroup of the bf16 kernel
 int bf16_block_m();
+int bf16_block_n();  // keys per tile
 // instantiation groups of the bf16 kernel, one translation unit each
 hipError_t launch_bf16_closed_form_d128(const AttnParams& p, hipStream_t stream);
 hipError_t launch_bf16_closed_form_d64(const AttnParams& p, hipStream_t stream);
@@ -33,5 +34,6 @@ hipError_t launch_combine(const AttnParams& p, int head_dim, bool bf16, hipStrea
 // fp32 inputs and arithmetic; head_dim 64 or 128.
 hipError_t launch_f32(const AttnParams& p, int head_dim, hipStream_t stream);
 int f32_block_m();
+int f32_block_n();  // keys per tile
 
 }  // namespace attn

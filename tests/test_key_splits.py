@@ -1,0 +1,135 @@
+"""Key splits of the prefill and fp32 kernels.
+
+Calls whose workgroups would not fill the chip leave partial results in the
+workspace. The cases cover rows written whole beside split ones (causal rows
+with few keys, a packed sequence with a short cache), splits that hold no tile
+of a row, ragged last splits, every normalisation, the general mask path, the
+relative position's LSE shift and fp32. Each must really be split
+(attn_workspace_bytes > 0), is run on a workspace full of NaN, and is compared
+with the fp64 oracle element by element at the bars of the other parity tests.
+"""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_05023_amd as attn
+from gpu_util import LSE_TOL, O_TOL, gpu_available, log
+from paper_2605_05023_amd import _abi
+from paper_2605_05023_amd.build import LIB_POISON
+from paper_2605_05023_amd.workloads import (MASK_CAUSAL, MASK_CAUSAL_BLOCKWISE, MASK_NAMES, MASK_NONE,
+                                            MASK_SHARE_QUESTION, MASK_SLIDING_WINDOW, alibi_slopes)
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+# (dtype, D, hq, hkv, [(lq, lk)] (packed when they differ), mask, options)
+CASES = [
+    ("bf16", 128, 2, 2, [(150, 4000)], MASK_CAUSAL, {}),
+    ("bf16", 128, 2, 2, [(2500, 2500)], MASK_CAUSAL, {}),
+    ("bf16", 64, 4, 4, [(200, 3001)], MASK_NONE, dict(alibi=True, softcap=50.0)),
+    ("bf16", 64, 3, 1, [(130, 3000)], MASK_CAUSAL, dict(relpos=True)),
+    ("bf16", 128, 8, 2, [(60, 3000), (200, 210), (1, 5000), (0, 40), (129, 0)], MASK_CAUSAL, {}),
+    ("bf16", 128, 4, 1, [(140, 4100)], MASK_SLIDING_WINDOW, dict(window=(3000, -1))),
+    ("bf16", 128, 2, 2, [(300, 3100)], MASK_CAUSAL, dict(norm="sigmoid")),
+    ("bf16", 64, 2, 2, [(300, 5100)], MASK_CAUSAL, dict(norm="relu", softcap=400.0)),
+    ("bf16", 128, 2, 2, [(2600, 2600)], MASK_SHARE_QUESTION, dict(seg=[900, 1500, 2300])),
+    ("bf16", 64, 2, 2, [(400, 5000)], MASK_CAUSAL_BLOCKWISE, dict(seg=[1000, 4700], query_start=4900,
+                                                                alibi=True, relpos=True)),
+    ("fp32", 128, 2, 2, [(1, 1500)], MASK_CAUSAL, dict(relpos=True)),
+    ("fp32", 64, 4, 2, [(70, 2001)], MASK_SLIDING_WINDOW, dict(window=(1500, 0), alibi=True)),
+    ("fp32", 128, 2, 1, [(600, 600)], MASK_CAUSAL, dict(norm="sigmoid")),
+    ("fp32", 64, 2, 2, [(33, 1600), (64, 64), (5, 900), (3, 0)], MASK_SHARE_QUESTION,
+     dict(seg=[500, 1000])),
+]
+NORMS = {"softmax": 0, "relu": 1, "sigmoid": 2}
+
+
+def _token_ids(starts, n):
+    return [sum(pos >= s for s in starts) - 1 for pos in range(n)]
+
+
+def _call(lib, q, k, v, packed, kw, softmax):
+    out = torch.empty_like(q)
+    lse = torch.empty(attn.lse_shape(q, packed), dtype=torch.float32, device=q.device) \
+        if softmax else None
+    d = attn.make_desc(q, k, v, out, **kw)
+    n = lib.attn_workspace_bytes(ctypes.byref(d))
+    assert n > 0, "the case is not split"
+    ws = torch.full((n,), 255, dtype=torch.uint8, device=q.device)  # NaN
+    st = lib.attn_fwd_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
+                         lse.data_ptr() if softmax else None, ctypes.byref(d), ws.data_ptr(), n)
+    assert st == 0
+    return out, lse
+
+
+@pytest.mark.parametrize("i", range(len(CASES)))
+def test_split_parity(i):
+    dtype, D, hq, hkv, lens, mask, opt = CASES[i]
+    log(f"[key splits] {CASES[i]}")
+    g = torch.Generator().manual_seed(77 + i)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    packed = len(set(lens)) > 1
+    lq, lk = [a for a, _ in lens], [b for _, b in lens]
+    qs = (sum(lq), hq, D) if packed else (len(lens), hq, lq[0], D)
+    ks = (sum(lk), hkv, D) if packed else (len(lens), hkv, lk[0], D)
+    q, k, v = (torch.randn(s, generator=g).to(tdt) for s in (qs, ks, ks))
+    norm = opt.get("norm", "softmax")
+    kw = dict(mask=MASK_NAMES[mask], softcap=opt.get("softcap", 0.0), norm=norm,
+              relative_position=opt.get("relpos", False), query_start=opt.get("query_start", 0))
+    okw = dict(mask=mask, softcap=opt.get("softcap", 0.0), norm=NORMS[norm],
+               relpos=opt.get("relpos", False), query_start=opt.get("query_start", 0))
+    if "window" in opt:
+        kw["window"] = opt["window"]
+        okw.update(window_left=opt["window"][0], window_right=opt["window"][1])
+    if opt.get("alibi"):
+        kw["alibi_slopes"] = alibi_slopes(hq).cuda()
+        okw["slopes"] = alibi_slopes(hq)
+    if "seg" in opt:
+        kw["segment_starts"] = torch.tensor(opt["seg"], dtype=torch.int32, device="cuda")
+        okw["token_ids"] = _token_ids(opt["seg"], max(lk))
+    if packed:
+        cuq, cuk = (torch.tensor([0] + list(np.cumsum(x)), dtype=torch.int32) for x in (lq, lk))
+        kw.update(cu_seqlens_q=cuq.cuda(), cu_seqlens_k=cuk.cuda(), max_seqlen_q=max(lq),
+                  max_seqlen_k=max(lk))
+        okw.update(cu_seqlens_q=cuq, cu_seqlens_k=cuk)
+    a = (q.cuda(), k.cuda(), v.cuda(), packed, kw, norm == "softmax")
+    o, lse = _call(attn.load(), *a)
+    o1, lse1 = _call(_abi.load(LIB_POISON), *a)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o1), "output differs with poisoned LDS"
+    o_ref, lse_ref = oracle.attention(q, k, v, scale=D ** -0.5, **okw)
+    og = o.float().cpu().numpy().astype(np.float64)
+    assert np.isfinite(og).all()
+    o_err, tol = float(np.abs(og - o_ref).max()), O_TOL[dtype]
+    if norm != "softmax":
+        tol *= float(np.abs(o_ref).max())
+    log(f"  max|dO| = {o_err:.3e} (tol {tol:.1e})")
+    assert o_err <= tol
+    if norm == "softmax":
+        lg = lse.cpu().numpy().astype(np.float64)
+        assert np.array_equal(np.isinf(lg), np.isinf(lse_ref))
+        fin = np.isfinite(lse_ref)
+        assert float(np.abs(lg[fin] - lse_ref[fin]).max()) <= LSE_TOL
+
+
+def test_two_streams_share_nothing():
+    """Split calls on two streams, interleaved: each gets the output of the
+    same call run alone (every call has a workspace of its own)."""
+    g = torch.Generator().manual_seed(5)
+    x = [[torch.randn(1, 4, n, 128, generator=g).to(torch.bfloat16).cuda() for n in (150, 4000, 4000)]
+         for _ in range(2)]
+    want = [attn.fwd(*t, causal=True) for t in x]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in x]
+    got = [[], []]
+    for _ in range(4):
+        for s, t, r in zip(streams, x, got):
+            with torch.cuda.stream(s):
+                r.append(attn.fwd(*t, causal=True))
+    torch.cuda.synchronize()
+    for w, r in zip(want, got):
+        for o, lse in r:
+            assert torch.equal(o, w[0]) and torch.equal(lse, w[1])
