@@ -39,6 +39,23 @@ _NORMS = {"softmax": ATTN_NORM_SOFTMAX, "relu": ATTN_NORM_RELU, "sigmoid": ATTN_
 _ORDERS = {None: 0, "natural": 1, "xcd_groups": 2}
 
 
+_native = None  # native argument marshalling (binding/fast.cpp), bound to libattn.so
+
+
+def _load_native():
+    global _native
+    lib = load()
+    try:
+        from . import _fast
+    except ImportError as e:
+        raise ImportError("the native binding is not built; run `python -m "
+                          "paper_2605_05023_amd.build`") from e
+    _fast.bind(ctypes.cast(lib.attn_fwd_ws, ctypes.c_void_p).value,
+               ctypes.cast(lib.attn_workspace_bytes, ctypes.c_void_p).value)
+    _native = _fast
+    return _fast
+
+
 def _int_array(t, name, device):
     if t.dtype != torch.int32 or t.device != device or not t.is_contiguous():
         raise TypeError(f"{name} must be contiguous int32 on q's device")
@@ -201,6 +218,15 @@ def fwd(q, k, v, *, causal: bool = False, window=None, alibi_slopes=None, softca
     `relative_position` and `norm` ("softmax", "relu", "sigmoid"; only softmax
     produces an LSE). See make_desc for `validate` and the schedule overrides.
     """
+    if not (validate or log or heads_per_wg or order or chunk):
+        res = (_native or _load_native()).fwd(
+            q, k, v, causal, window, alibi_slopes, softcap, scale, cu_seqlens_q, cu_seqlens_k,
+            max_seqlen_q, max_seqlen_k, out, lse, return_lse, mask, prefix_len, num_global,
+            global_tokens, segment_starts, query_start, relative_position, norm)
+        if res is not NotImplemented:
+            return res
+    # options and arguments that the native marshalling does not take, and
+    # everything that is an error
     if not q.is_cuda:
         raise ValueError("fwd runs on the GPU only; q, k, v must be device tensors")
     lib = load()

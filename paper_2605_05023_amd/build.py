@@ -1,4 +1,5 @@
-"""Build libattn.so (HIP kernels for gfx950 plus the C ABI) in-tree.
+"""Build libattn.so (HIP kernels for gfx950 plus the C ABI) and the native
+argument marshalling of the Python binding (_fast) in-tree.
 
     python -m paper_2605_05023_amd.build               # libattn.so
     python -m paper_2605_05023_amd.build --lds-poison  # libattn_poison.so
@@ -15,6 +16,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -57,12 +59,36 @@ def _compile(src: str, poison: bool = False) -> str:
     return obj
 
 
+def _build_binding() -> str:
+    """_fast: plain host C++ against torch's libraries (already loaded wherever it is imported)."""
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    out = os.path.join(PKG, "_fast" + sysconfig.get_config_var("EXT_SUFFIX"))
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-isystem", os.path.join(troot, "include"),
+           "-isystem", os.path.join(troot, "include", "torch", "csrc", "api", "include"),
+           "-isystem", "/opt/rocm/include", "-I", sysconfig.get_paths()["include"],
+           os.path.join(PKG, "binding", "fast.cpp"), "-L", os.path.join(troot, "lib"), "-lc10",
+           "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch", "-ltorch_python", "-o", out + ".tmp"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{res.stderr}")
+    if res.stderr.strip():
+        sys.stderr.write(res.stderr)
+    os.replace(out + ".tmp", out)
+    return out
+
+
 def build(verbose: bool = False, poison: bool = False) -> str:
     lib = LIB_POISON if poison else LIB
     os.makedirs(BUILD_DIR + ("_poison" if poison else ""), exist_ok=True)
     srcs = sources()
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+        binding = None if poison else ex.submit(_build_binding)
         objs = list(ex.map(lambda s: _compile(s, poison), srcs))
+        if binding is not None:
+            binding.result()
     tmp = lib + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     subprocess.run(cmd, check=True)

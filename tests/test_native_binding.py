@@ -1,0 +1,118 @@
+"""The native argument marshalling against the Python path it stands in for:
+the same descriptor (the launch plan printed by the log flag apart, which only
+the Python path takes), the same outputs bit for bit, and the same refusals.
+"""
+import pytest
+import torch
+
+import paper_2605_05023_amd as attn
+from gpu_util import gpu_available, log
+from paper_2605_05023_amd.workloads import alibi_slopes
+
+gpu = pytest.mark.gpu
+needs_gpu = pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
+
+
+def _x(*shape, dtype=torch.bfloat16, seed=0):
+    g = torch.Generator().manual_seed(seed + sum(shape))
+    return torch.randn(*shape, generator=g).to(dtype).cuda()
+
+
+def _i32(v):
+    return torch.tensor(v, dtype=torch.int32, device="cuda")
+
+
+def _cases():
+    q, k, v = _x(2, 8, 70, 64), _x(2, 2, 90, 64), _x(2, 2, 90, 64, seed=1)
+    pq, pk, pv = _x(130, 4, 128), _x(200, 2, 128), _x(200, 2, 128, seed=1)
+    cu = dict(cu_seqlens_q=_i32([0, 30, 130]), cu_seqlens_k=_i32([0, 80, 200]), max_seqlen_q=100,
+              max_seqlen_k=120)
+    f = torch.float32
+    bshd = [t.transpose(1, 2) for t in (_x(1, 50, 4, 64), _x(1, 50, 4, 64), _x(1, 50, 4, 64, seed=1))]
+    out, lse = torch.empty_like(q), torch.empty(2, 8, 70, device="cuda")
+    return [
+        ((q, k, v), {}),
+        ((q, k, v), dict(causal=True, return_lse=False)),
+        ((q, k, v), dict(causal=True, out=out, lse=lse)),
+        ((q, k, v), dict(window=(20, 3), scale=0.2, softcap=30)),
+        ((q, k, v), dict(mask="prefix_lm", prefix_len=11, alibi_slopes=alibi_slopes(8).cuda())),
+        ((q, k, v), dict(mask=4, window=(9, 9), num_global=3, relative_position=True)),
+        ((q, k, v), dict(mask="global_sliding_window", window=(9, -1), global_tokens=_i32([1, 40, 77]))),
+        ((q, k, v), dict(mask="share_question", segment_starts=_i32([[20, 50], [30, 60]]))),
+        ((q, k, v), dict(mask="causal_blockwise", segment_starts=_i32([20, 50]), query_start=60,
+                         norm="relu")),
+        ((q, k, v), dict(causal=True, norm=2)),
+        (tuple(bshd), dict(causal=True)),
+        ((_x(1, 2, 40, 64, dtype=f), _x(1, 2, 40, 64, dtype=f), _x(1, 2, 40, 64, dtype=f, seed=1)), {}),
+        ((pq, pk, pv), dict(causal=True, **cu)),
+        ((q[:, :, :1], k, v), dict(causal=True)),
+    ]
+
+
+@gpu
+@needs_gpu
+def test_same_outputs_as_the_python_path():
+    for i, (x, kw) in enumerate(_cases()):
+        log(f"[native binding] case {i} {sorted(kw)}")
+        assert attn._load_native() is not None
+        got = attn.fwd(*x, **kw)
+        got = [t.clone() for t in (got if isinstance(got, tuple) else (got,))]
+        want = attn.fwd(*x, **kw, validate=True)  # taken by the Python path
+        want = want if isinstance(want, tuple) else (want,)
+        torch.cuda.synchronize()
+        assert len(got) == len(want)
+        for a, b in zip(got, want):
+            assert a.shape == b.shape and a.stride() == b.stride() and torch.equal(a, b)
+
+
+@gpu
+@needs_gpu
+def test_given_outputs_come_back():
+    q, k, v = _x(1, 2, 20, 64), _x(1, 2, 20, 64), _x(1, 2, 20, 64, seed=1)
+    out, lse = torch.empty_like(q), torch.empty(1, 2, 20, device="cuda")
+    o, l = attn.fwd(q, k, v, out=out, lse=lse)
+    assert o is out and l is lse
+    assert attn.fwd(q, k, v, out=out, lse=lse, return_lse=False) is out
+
+
+@gpu
+@needs_gpu
+def test_refusals_are_those_of_the_python_path():
+    q, k, v = _x(1, 4, 20, 64), _x(1, 2, 20, 64), _x(1, 2, 20, 64, seed=1)
+    for err, x, kw in [
+        (TypeError, (q, k.float(), v), {}),
+        (ValueError, (q, k, v[:, :, :19]), {}),
+        (ValueError, (q.transpose(2, 3), k, v), {}),
+        (ValueError, (q, k, v), dict(alibi_slopes=torch.ones(3, device="cuda"))),
+        (TypeError, (q, k, v), dict(alibi_slopes=torch.ones(4))),
+        (TypeError, (q, k, v), dict(lse=torch.empty(1, 4, 20))),
+        (ValueError, (q, k, v), dict(out=torch.empty_like(q)[:, :, :5])),
+        (KeyError, (q, k, v), dict(mask="diagonal")),
+        (ValueError, (q[0].transpose(0, 1), k[0].transpose(0, 1), v[0].transpose(0, 1)),
+         dict(cu_seqlens_q=_i32([0, 20]))),
+        (attn.AttnError, (q, k, v), dict(window=(-2, 0))),
+        (attn.AttnError, (q, k, v), dict(scale=-1.0)),
+        (attn.AttnError, (_x(1, 3, 20, 64), k, v), {}),
+        (ValueError, (q.cpu(), k.cpu(), v.cpu()), {}),
+    ]:
+        with pytest.raises(err):
+            attn.fwd(*x, **kw)
+
+
+@gpu
+@needs_gpu
+def test_subclasses_and_modes_take_the_python_path():
+    class Sub(torch.Tensor):
+        pass
+
+    q, k, v = _x(1, 2, 20, 64), _x(1, 2, 20, 64), _x(1, 2, 20, 64, seed=1)
+    args = (False, None, None, 0.0, None, None, None, None, None, None, None, True, None, 0, 0, None,
+            None, 0, False, "softmax")
+    native = attn._load_native()
+    assert native.fwd(q, k, v, *args) is not NotImplemented
+    assert native.fwd(q.as_subclass(Sub), k, v, *args) is NotImplemented
+    with torch.utils._python_dispatch.TorchDispatchMode():
+        assert native.fwd(q, k, v, *args) is NotImplemented
+    o = torch.empty(20, 64)
+    assert torch.func.vmap(lambda t: o if native.fwd(t, t, t, *args) is NotImplemented else t[0, 0])(
+        torch.stack([q, q])).shape == (2, 20, 64)
