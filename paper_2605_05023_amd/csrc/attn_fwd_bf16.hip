@@ -10,27 +10,9 @@ namespace attn {
 int bf16_block_m() { return BM; }
 int bf16_block_n() { return key_tile_width(0); }
 
-namespace {
-
-template <int D, bool LEFT>
-hipError_t launch_closed_form(const AttnParams& p, hipStream_t stream)
-{
-    const int bias = p.slopes ? kBiasAlibi : (p.relpos ? kBiasRelPos : kBiasNone);
-    return with_cap(p, [&](auto cap) {
-        constexpr int C = decltype(cap)::value;
-        if (bias == kBiasAlibi) return launch_variant<D, C, kBiasAlibi, kNormSoftmax, false, LEFT>(p, stream);
-        if (bias == kBiasRelPos) return launch_variant<D, C, kBiasRelPos, kNormSoftmax, false, LEFT>(p, stream);
-        return launch_variant<D, C, kBiasNone, kNormSoftmax, false, LEFT>(p, stream);
-    });
-}
-
-}  // namespace
-
 hipError_t launch_bf16_closed_form_d128(const AttnParams& p, hipStream_t stream)
 {
-    // a left-bounded band (sliding window) checks both bounds on partial tiles
-    return p.band.wl >= 0 ? launch_closed_form<128, true>(p, stream)
-                          : launch_closed_form<128, false>(p, stream);
+    return launch_closed_form<128, false>(p, stream);
 }
 
 hipError_t launch_bf16(const AttnParams& p, int head_dim, hipStream_t stream)
@@ -41,6 +23,13 @@ hipError_t launch_bf16(const AttnParams& p, int head_dim, hipStream_t stream)
         if (p.norm == kNormRelu) return launch_bf16_glist_relu(p, head_dim, stream);
         if (p.norm == kNormSigmoid) return launch_bf16_glist_sigmoid(p, head_dim, stream);
         return launch_bf16_glist_softmax(p, head_dim, stream);
+    }
+    if (p.splits > 1) {
+        if (p.norm == kNormRelu) return launch_bf16_split_general_relu(p, head_dim, stream);
+        if (p.norm == kNormSigmoid) return launch_bf16_split_general_sigmoid(p, head_dim, stream);
+        if (!closed || both_biases) return launch_bf16_split_general_softmax(p, head_dim, stream);
+        return head_dim == 128 ? launch_bf16_split_closed_form_d128(p, stream)
+                               : launch_bf16_split_closed_form_d64(p, stream);
     }
     if (p.norm == kNormRelu) return launch_bf16_general_relu(p, head_dim, stream);
     if (p.norm == kNormSigmoid) return launch_bf16_general_sigmoid(p, head_dim, stream);

@@ -1,0 +1,12 @@
+// attn_fwd_bf16_split_d128.hip -- head-dim-128 instantiations of the
+// closed-form-mask softmax kernels with the keys split over workgroups.
+#include "bf16_kernel.h"
+
+namespace attn {
+
+hipError_t launch_bf16_split_closed_form_d128(const AttnParams& p, hipStream_t stream)
+{
+    return launch_closed_form<128, true>(p, stream);
+}
+
+}  // namespace attn

@@ -1,0 +1,12 @@
+// attn_fwd_bf16_split_general_relu.hip -- general-path bf16 kernels with the
+// relu normalisation and the keys split over workgroups.
+#include "bf16_kernel.h"
+
+namespace attn {
+
+hipError_t launch_bf16_split_general_relu(const AttnParams& p, int head_dim, hipStream_t stream)
+{
+    return launch_general_norm<kNormRelu, false, true>(p, head_dim, stream);
+}
+
+}  // namespace attn

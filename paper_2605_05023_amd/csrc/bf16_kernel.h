@@ -93,11 +93,16 @@ constexpr float PSUM_BOUND = 256.0f;
 // GLIST: the global sliding window's global set is a listed set of positions
 // (general path only); its keys outside a row's band are visited after the
 // planned tiles as gathered tiles.
+// SPLIT: the grid's second axis splits each work item's key tiles. Kernels of
+// their own, chosen when the host splits: one kernel for both shifted the
+// register allocation of the unsplit calls (D = 64 ReLU 168 -> 169 registers,
+// three -> two workgroups per CU, 4 % slower; others within 2 % either way).
 template <int D_, int BN_, int CAP_, int BIAS_, int NORM_, bool GEN_, bool LEFT_ = true,
-          bool GLIST_ = false>
+          bool GLIST_ = false, bool SPLIT_ = false>
 struct Traits {
     static constexpr int D = D_, BN = BN_;
-    static constexpr bool GLIST = GLIST_;
+    static constexpr bool GLIST = GLIST_, SPLIT = SPLIT_;
+    static_assert(!GLIST_ || !SPLIT_, "a listed global set is not split");
     static_assert(!GLIST_ || GEN_, "a listed global set takes the general path");
     static constexpr int CAP = CAP_;
     static constexpr bool SOFTCAP = CAP_ != kCapOff, MODS = SOFTCAP || BIAS_ != kBiasNone;
@@ -257,19 +262,6 @@ __device__ __forceinline__ float pair_sum(float x)
 struct WorkItem {
     int b, hq, hkv, qt;
 };
-
-// The kernel arguments read at the point of the call: through a pointer that
-// the compiler cannot see through, so that what only a workgroup's last step
-// uses (output pointers and strides) is not loaded at entry and carried, or
-// spilled, through the key loop in scalar registers.
-typedef const __attribute__((address_space(4))) AttnParams KernArg;
-
-__device__ __forceinline__ KernArg& late_args()
-{
-    KernArg* a = (KernArg*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(a));
-    return *a;
-}
 
 // Compile-time loop: f(std::integral_constant<int, i>) for i = 0..N-1, so
 // every index is a constant and per-iteration arrays stay in registers.
@@ -1150,11 +1142,9 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_bf16_kernel(AttnParams p)
                  "s"(p.div_hq.shift), "s"(p.div_hq.d), "s"(p.div_group.mul),
                  "s"(p.div_group.shift), "s"(p.div_group.d), "s"(p.div_hkv.mul),
                  "s"(p.div_hkv.shift), "s"(p.div_hkv.d), "s"(p.cu_q), "s"(p.seqlen_q),
-                 "s"(p.seqlen_k), "s"(p.wg_rows), "s"(p.q), "s"(p.k), "s"(p.v),
+                 "s"(p.seqlen_k), "s"(p.wg_rows), "s"(p.q), "s"(p.k), "s"(p.v), "s"(p.o),
                  "s"(p.sq_b), "s"(p.sq_h), "s"(p.sq_s), "s"(p.sk_b), "s"(p.sk_h), "s"(p.sk_s),
-                 "s"(p.sv_b), "s"(p.sv_h), "s"(p.sv_s));
-    // blockIdx.y is the key split: an item's splits meet on its XCD when the
-    // item count is a multiple of 8.
+                 "s"(p.sv_b), "s"(p.sv_h), "s"(p.sv_s), "s"(p.so_h), "s"(p.so_s));
     // Listed global set: the first glob_items workgroups compute the rows
     // whose position is in G (every key visible), wg_rows list entries each,
     // for one head set of one sequence; the others are the ordinary work
@@ -1201,13 +1191,16 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_bf16_kernel(AttnParams p)
     const __bf16* qb = static_cast<const __bf16*>(p.q);
     const __bf16* kbase = static_cast<const __bf16*>(p.k);
     const __bf16* vbase = static_cast<const __bf16*>(p.v);
-    int64_t qoff, koff, voff;
+    __bf16* ob = static_cast<__bf16*>(p.o);
+    int64_t qoff, koff, voff, ooff;
     if (p.cu_q) {
         qoff = qrow0 * p.sq_s + (int64_t)hq * p.sq_h;
+        ooff = qrow0 * p.so_s + (int64_t)hq * p.so_h;
         koff = krow0 * p.sk_s + (int64_t)hkv * p.sk_h;
         voff = krow0 * p.sv_s + (int64_t)hkv * p.sv_h;
     } else {
         qoff = (int64_t)it.b * p.sq_b + (int64_t)hq * p.sq_h;
+        ooff = (int64_t)it.b * p.so_b + (int64_t)hq * p.so_h;
         koff = (int64_t)it.b * p.sk_b + (int64_t)hkv * p.sk_h;
         voff = (int64_t)it.b * p.sv_b + (int64_t)hkv * p.sv_h;
     }
@@ -1317,23 +1310,20 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_bf16_kernel(AttnParams p)
         jbeg = 0;
         jend = gp.hi - gp.lo;
     }
-    // index of this lane's row in the LSE
-    auto lse_row = [&](const KernArg& a) __attribute__((always_inline)) -> int64_t {
-        return a.cu_q ? (int64_t)hq * a.total_q + a.cu_q[it.b] + qi
-                      : ((int64_t)it.b * a.hq + hq) * lq + qi;
-    };
     // This split's share of the visited tiles. An item with no more tiles than
     // one split takes is written by its first split as if it were not split.
-    const uint32_t sp = blockIdx.y;
-    bool partial = false;
-    if (p.splits > 1) {
+    [[maybe_unused]] auto lse_row = [&]() __attribute__((always_inline)) -> int64_t {
+        return p.cu_q ? (int64_t)hq * p.total_q + qrow0 + qi : ((int64_t)it.b * p.hq + hq) * lq + qi;
+    };
+    [[maybe_unused]] bool partial = false;
+    if constexpr (T::SPLIT) {
+        const int sp = blockIdx.y;
         partial = jend - jbeg > p.split_tiles;
-        jbeg += (int)sp * p.split_tiles;
-        if ((int)sp < p.splits - 1) jend = min(jend, jbeg + p.split_tiles);
+        jbeg += sp * p.split_tiles;
+        if (sp < p.splits - 1) jend = min(jend, jbeg + p.split_tiles);
         if (sp > 0 && jbeg >= jend) {  // no tiles: an empty partial
-            const KernArg& a = late_args();
             if (row_ok && lh == 0)
-                *reinterpret_cast<f32x4*>(a.ws_ml + (sp * a.ws_rows + lse_row(a)) * 4) =
+                *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.ws_rows + lse_row()) * 4) =
                     f32x4{-__builtin_inff(), 0.0f, 0.0f, 0.0f};
             return;
         }
@@ -1512,8 +1502,8 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_bf16_kernel(AttnParams p)
             phase(Bool<false>{}, run_end(j + 1, 1 + kSideRight), Right{});
             phase(Bool<true>{}, jend, Both{});
         } else {
-            phase(Bool<true>{}, min(gp.full_lo, jend), Both{});
-            phase(Bool<false>{}, min(gp.full_hi, jend), Both{});
+            phase(Bool<true>{}, T::SPLIT ? min(gp.full_lo, jend) : gp.full_lo, Both{});
+            phase(Bool<false>{}, T::SPLIT ? min(gp.full_hi, jend) : gp.full_hi, Both{});
             phase(Bool<true>{}, jend, Both{});
         }
         rescale_if_needed(ws);
@@ -1541,36 +1531,35 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_bf16_kernel(AttnParams p)
     } else {
         inv = lk > 0 ? 1.0f / (float)lk : 0.0f;
     }
-    const KernArg& a = late_args();
-    if (partial) {
-        // unnormalised O (ReLU, Sigmoid: the share of O) and the row's scalars
-        if (row_ok) {
-            const int64_t prt = sp * a.ws_rows + lse_row(a);
-            float* prow = a.ws_o + prt * D;
-            const float scale = T::SOFTMAX ? 1.0f : inv;
+    if constexpr (T::SPLIT) {
+        if (partial) {
+            // unnormalised O (ReLU, Sigmoid: the share of O) and the row's scalars
+            if (row_ok) {
+                const int64_t prt = blockIdx.y * p.ws_rows + lse_row();
+                float* prow = p.ws_o + prt * D;
+                const float scale = T::SOFTMAX ? 1.0f : inv;
 #pragma unroll
-            for (int d = 0; d < T::DBLK; ++d)
+                for (int d = 0; d < T::DBLK; ++d)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    f32x4 x;
+                    for (int q = 0; q < 4; ++q) {
+                        f32x4 x;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) x[e] = ws.oacc[d][4 * q + e] * scale;
-                    *reinterpret_cast<f32x4*>(prow + 32 * d + 16 * (q / 2) + 8 * lh + 4 * (q % 2)) = x;
-                }
-            f32x4 sc = {0.0f, 1.0f, 1.0f, 0.0f};
-            if constexpr (T::SOFTMAX)
-                sc = f32x4{ws.m_run, l_tot, lo_tot,
-                           ws.bias_lin != 0.0f ? (float)(ws.ip - ws.jref) : 0.0f};
-            if (lh == 0) *reinterpret_cast<f32x4*>(a.ws_ml + prt * 4) = sc;
+                        for (int e = 0; e < 4; ++e) x[e] = ws.oacc[d][4 * q + e] * scale;
+                        *reinterpret_cast<f32x4*>(prow + 32 * d + 16 * (q / 2) + 8 * lh + 4 * (q % 2)) = x;
+                    }
+                f32x4 sc = {0.0f, 1.0f, 1.0f, 0.0f};
+                if constexpr (T::SOFTMAX)
+                    sc = f32x4{ws.m_run, l_tot, lo_tot,
+                               ws.bias_lin != 0.0f ? (float)(ws.ip - ws.jref) : 0.0f};
+                if (lh == 0) *reinterpret_cast<f32x4*>(p.ws_ml + prt * 4) = sc;
+            }
+            return;
         }
-        return;
+        if (row_ok && lh == 0)  // written here: nothing to combine
+            *reinterpret_cast<f32x4*>(p.ws_ml + lse_row() * 4) = f32x4{0.0f, 0.0f, -1.0f, 0.0f};
     }
     if (row_ok) {
-        if (a.splits > 1 && lh == 0)  // written here: nothing to combine
-            *reinterpret_cast<f32x4*>(a.ws_ml + lse_row(a) * 4) = f32x4{0.0f, 0.0f, -1.0f, 0.0f};
-        __bf16* orow = static_cast<__bf16*>(a.o) + (int64_t)hq * a.so_h +
-                       (a.cu_q ? ((int64_t)a.cu_q[it.b] + qi) * a.so_s
-                               : (int64_t)it.b * a.so_b + (int64_t)qi * a.so_s);
+        __bf16* orow = ob + ooff + (int64_t)qi * p.so_s;
 #pragma unroll
         for (int d = 0; d < T::DBLK; ++d) {
 #pragma unroll
@@ -1583,13 +1572,15 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_bf16_kernel(AttnParams p)
             }
         }
         if constexpr (T::SOFTMAX) {
-            if (a.lse && lh == 0) {
+            if (p.lse && lh == 0) {
                 float lse = -__builtin_inff();
                 if (l_tot > 0.0f) {
                     lse = (ws.m_run + __builtin_log2f(l_tot)) * kLn2;
                     if (ws.bias_lin != 0.0f) lse += (float)(ws.ip - ws.jref);
                 }
-                a.lse[lse_row(a)] = lse;
+                int64_t idx = p.cu_q ? (int64_t)hq * p.total_q + qrow0 + qi
+                                     : ((int64_t)it.b * p.hq + hq) * lq + qi;
+                p.lse[idx] = lse;
             }
         }
     }
@@ -1600,12 +1591,13 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_bf16_kernel(AttnParams p)
 // scores in the registers of two waves per SIMD.
 constexpr int key_tile_width(int) { return 64; }
 
-template <int D, int CAP, int BIAS, int NORM, bool GEN, bool LEFT = true, bool GLIST = false>
+template <int D, int CAP, int BIAS, int NORM, bool GEN, bool LEFT = true, bool GLIST = false,
+          bool SPLIT = false>
 hipError_t launch_variant(const AttnParams& p, hipStream_t stream)
 {
-    using T = Traits<D, key_tile_width(D), CAP, BIAS, NORM, GEN, LEFT, GLIST>;
-    hipLaunchKernelGGL((attn_fwd_bf16_kernel<T>), dim3((unsigned)p.grid, (unsigned)p.splits), dim3(NT), 0,
-                       stream, p);
+    using T = Traits<D, key_tile_width(D), CAP, BIAS, NORM, GEN, LEFT, GLIST, SPLIT>;
+    hipLaunchKernelGGL((attn_fwd_bf16_kernel<T>), dim3((unsigned)p.grid, (unsigned)(SPLIT ? p.splits : 1)),
+                       dim3(NT), 0, stream, p);
     return hipGetLastError();
 }
 
@@ -1625,18 +1617,41 @@ hipError_t with_cap(const AttnParams& p, F&& f)
 // The general-path instantiations of one normalisation: head dim, soft-cap,
 // and a runtime-coefficient bias when ALiBi or the relative position is on;
 // GLIST for a listed global set.
-template <int NORM, bool GLIST = false>
+template <int NORM, bool GLIST = false, bool SPLIT = false>
 hipError_t launch_general_norm(const AttnParams& p, int head_dim, hipStream_t stream)
 {
     const bool bias = p.slopes != nullptr || p.relpos != 0;
     return with_cap(p, [&](auto cap) {
         constexpr int C = decltype(cap)::value;
         if (head_dim == 128)
-            return bias ? launch_variant<128, C, kBiasGeneral, NORM, true, true, GLIST>(p, stream)
-                        : launch_variant<128, C, kBiasNone, NORM, true, true, GLIST>(p, stream);
-        return bias ? launch_variant<64, C, kBiasGeneral, NORM, true, true, GLIST>(p, stream)
-                    : launch_variant<64, C, kBiasNone, NORM, true, true, GLIST>(p, stream);
+            return bias ? launch_variant<128, C, kBiasGeneral, NORM, true, true, GLIST, SPLIT>(p, stream)
+                        : launch_variant<128, C, kBiasNone, NORM, true, true, GLIST, SPLIT>(p, stream);
+        return bias ? launch_variant<64, C, kBiasGeneral, NORM, true, true, GLIST, SPLIT>(p, stream)
+                    : launch_variant<64, C, kBiasNone, NORM, true, true, GLIST, SPLIT>(p, stream);
     });
+}
+
+// The closed-form-mask softmax instantiations of one head dim. A left-bounded
+// band (sliding window) checks both bounds on partial tiles.
+template <int D, bool LEFT, bool SPLIT>
+hipError_t launch_closed_form_left(const AttnParams& p, hipStream_t stream)
+{
+    const int bias = p.slopes ? kBiasAlibi : (p.relpos ? kBiasRelPos : kBiasNone);
+    return with_cap(p, [&](auto cap) {
+        constexpr int C = decltype(cap)::value;
+        if (bias == kBiasAlibi)
+            return launch_variant<D, C, kBiasAlibi, kNormSoftmax, false, LEFT, false, SPLIT>(p, stream);
+        if (bias == kBiasRelPos)
+            return launch_variant<D, C, kBiasRelPos, kNormSoftmax, false, LEFT, false, SPLIT>(p, stream);
+        return launch_variant<D, C, kBiasNone, kNormSoftmax, false, LEFT, false, SPLIT>(p, stream);
+    });
+}
+
+template <int D, bool SPLIT>
+hipError_t launch_closed_form(const AttnParams& p, hipStream_t stream)
+{
+    return p.band.wl >= 0 ? launch_closed_form_left<D, true, SPLIT>(p, stream)
+                          : launch_closed_form_left<D, false, SPLIT>(p, stream);
 }
 
 }  // namespace

@@ -18,6 +18,12 @@ hipError_t launch_bf16_closed_form_d64(const AttnParams& p, hipStream_t stream);
 hipError_t launch_bf16_general_softmax(const AttnParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_bf16_general_relu(const AttnParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_bf16_general_sigmoid(const AttnParams& p, int head_dim, hipStream_t stream);
+// the same with the keys split over workgroups (p.splits > 1)
+hipError_t launch_bf16_split_closed_form_d128(const AttnParams& p, hipStream_t stream);
+hipError_t launch_bf16_split_closed_form_d64(const AttnParams& p, hipStream_t stream);
+hipError_t launch_bf16_split_general_softmax(const AttnParams& p, int head_dim, hipStream_t stream);
+hipError_t launch_bf16_split_general_relu(const AttnParams& p, int head_dim, hipStream_t stream);
+hipError_t launch_bf16_split_general_sigmoid(const AttnParams& p, int head_dim, hipStream_t stream);
 // general path with a listed global set (global sliding window), per normalisation
 hipError_t launch_bf16_glist_softmax(const AttnParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_bf16_glist_relu(const AttnParams& p, int head_dim, hipStream_t stream);
