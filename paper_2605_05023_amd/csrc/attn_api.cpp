@@ -653,6 +653,13 @@ int plan_launch(const attn_variant_desc& d, AttnParams& p, const CallShape& c)
         p.glob_items = (int32_t)items;
         p.grid += p.glob_items;
     }
+    // Third workgroup per CU for D = 64 (where compiled: no score mods, no left
+    // bound) on long sequences and grids of about three rounds and more: 4 x 16
+    // heads of 3000 causal rows 95 -> 90 us, 4096 164 -> 157, 2 x 16 x 8000
+    // without a mask 554 -> 545; below, its spills at start-up and the uneven
+    // last round cost more (4 x 16 x 1000 18.6 against 20.2, 32 x 16 x 500 41.7
+    // against 43.6, packed lengths of 100..3000 182 against 183).
+    p.wide = D == 64 && p.grid >= 1500 && (varlen ? d.total_k / d.batch : d.seqlen_k) >= 2560;
     p.decode = 0;
     p.splits = 1;
     p.split_tiles = 1 << 30;

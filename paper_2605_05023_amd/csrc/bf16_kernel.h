@@ -98,8 +98,9 @@ constexpr float PSUM_BOUND = 256.0f;
 // register allocation of the unsplit calls (D = 64 ReLU 168 -> 169 registers,
 // three -> two workgroups per CU, 4 % slower; others within 2 % either way).
 template <int D_, int BN_, int CAP_, int BIAS_, int NORM_, bool GEN_, bool LEFT_ = true,
-          bool GLIST_ = false, bool SPLIT_ = false>
+          bool GLIST_ = false, bool SPLIT_ = false, int WGS_ = 2>
 struct Traits {
+    static constexpr int WGS = WGS_;  // workgroups per CU that the registers allow
     static constexpr int D = D_, BN = BN_;
     static constexpr bool GLIST = GLIST_, SPLIT = SPLIT_;
     static_assert(!GLIST_ || !SPLIT_, "a listed global set is not split");
@@ -1107,7 +1108,7 @@ __device__ TileRanges plan_general(RowVis r, bool valid, int (*red)[8], int wave
 }
 
 template <class T>
-__global__ __launch_bounds__(NT, 2) void attn_fwd_bf16_kernel(AttnParams p)
+__global__ __launch_bounds__(NT, T::WGS) void attn_fwd_bf16_kernel(AttnParams p)
 {
     constexpr int D = T::D, BN = T::BN;
     // Separate LDS objects per buffer: the compiler can then prove that reads
@@ -1592,10 +1593,10 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_bf16_kernel(AttnParams p)
 constexpr int key_tile_width(int) { return 64; }
 
 template <int D, int CAP, int BIAS, int NORM, bool GEN, bool LEFT = true, bool GLIST = false,
-          bool SPLIT = false>
+          bool SPLIT = false, int WGS = 2>
 hipError_t launch_variant(const AttnParams& p, hipStream_t stream)
 {
-    using T = Traits<D, key_tile_width(D), CAP, BIAS, NORM, GEN, LEFT, GLIST, SPLIT>;
+    using T = Traits<D, key_tile_width(D), CAP, BIAS, NORM, GEN, LEFT, GLIST, SPLIT, WGS>;
     hipLaunchKernelGGL((attn_fwd_bf16_kernel<T>), dim3((unsigned)p.grid, (unsigned)(SPLIT ? p.splits : 1)),
                        dim3(NT), 0, stream, p);
     return hipGetLastError();
@@ -1631,7 +1632,9 @@ hipError_t launch_general_norm(const AttnParams& p, int head_dim, hipStream_t st
     });
 }
 
-// The closed-form-mask softmax instantiations of one head dim. A left-bounded
+// The closed-form-mask softmax instantiations of one head dim. D = 64 without
+// score mods or a left bound also with registers for three workgroups per CU
+// (p.wide; 7 registers spill, outside the products). A left-bounded
 // band (sliding window) checks both bounds on partial tiles.
 template <int D, bool LEFT, bool SPLIT>
 hipError_t launch_closed_form_left(const AttnParams& p, hipStream_t stream)
@@ -1643,6 +1646,10 @@ hipError_t launch_closed_form_left(const AttnParams& p, hipStream_t stream)
             return launch_variant<D, C, kBiasAlibi, kNormSoftmax, false, LEFT, false, SPLIT>(p, stream);
         if (bias == kBiasRelPos)
             return launch_variant<D, C, kBiasRelPos, kNormSoftmax, false, LEFT, false, SPLIT>(p, stream);
+        if constexpr (D == 64 && C == kCapOff && !LEFT && !SPLIT) {
+            if (p.wide)
+                return launch_variant<D, C, kBiasNone, kNormSoftmax, false, LEFT, false, SPLIT, 3>(p, stream);
+        }
         return launch_variant<D, C, kBiasNone, kNormSoftmax, false, LEFT, false, SPLIT>(p, stream);
     });
 }

@@ -99,6 +99,7 @@ struct AttnParams {
     // caller's workspace for attn_combine: ws_o [splits][ws_rows][D] and ws_ml
     // [splits][ws_rows][4] (running max, fp32 row sum, the sum that normalises
     // O, LSE shift), rows indexed as the LSE. splits = 1: no workspace.
+    int32_t wide;            // bf16, D = 64: three workgroups per CU where compiled
     int32_t decode;          // bf16 decode kernel (num_q_tiles: its row tiles)
     int32_t splits, split_tiles;
     int64_t ws_rows;

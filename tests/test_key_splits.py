@@ -133,3 +133,20 @@ def test_two_streams_share_nothing():
     for w, r in zip(want, got):
         for o, lse in r:
             assert torch.equal(o, w[0]) and torch.equal(lse, w[1])
+
+
+@pytest.mark.parametrize("mask,lk", [(MASK_NONE, 2560), (MASK_CAUSAL, 2561), (MASK_CAUSAL, 2559)])
+def test_third_workgroup_per_cu(mask, lk):
+    """D = 64 on both sides of the rule (2560 keys, 1500 workgroups) that gives a
+    CU a third workgroup; sampled rows against the oracle."""
+    lq, h = 385, 512  # 4 query tiles, the last one with one row
+    g = torch.Generator(device="cuda").manual_seed(lk)
+    q, k, v = (torch.randn(1, h, n, 64, generator=g, device="cuda").to(torch.bfloat16)
+               for n in (lq, lk, lk))
+    o, lse = attn.fwd(q, k, v, mask=MASK_NAMES[mask])
+    torch.cuda.synchronize()
+    for head in (0, 255, 511):
+        one = [t[:, head:head + 1].cpu() for t in (q, k, v)]
+        o_ref, lse_ref = oracle.attention(*one, scale=0.125, mask=mask)
+        assert float(np.abs(o[:, head:head + 1].float().cpu().numpy() - o_ref).max()) <= O_TOL["bf16"]
+        assert float(np.abs(lse[:, head:head + 1].cpu().numpy() - lse_ref).max()) <= LSE_TOL
