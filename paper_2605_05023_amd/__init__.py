@@ -1,9 +1,11 @@
 """MI355X (gfx950) fused attention forward.
 
 `fwd` marshals torch tensors (device memory and the current stream) into an
-`attn_variant_desc` and calls `attn_fwd` of libattn.so. The computation runs
+`attn_variant_desc` and calls `attn_fwd_ws` of libattn.so, with a workspace
+from torch's allocator where the library can use one. The computation runs
 entirely in the library's HIP kernels; if the library is missing the import
-of `fwd`'s backend fails loudly.
+of `fwd`'s backend fails loudly. Ordinary calls are marshalled natively
+(binding/fast.cpp), the others and every error by the code below.
 
 The C ABI sees only pointers, so every shape is checked here against q before
 the call: a mismatch raises ValueError (TypeError for a dtype or device) and

@@ -743,7 +743,9 @@ extern "C" int attn_fwd_ws(const void* q, const void* k, const void* v, void* ou
     p.o = out;
     p.lse = lse;
     const int64_t need = workspace_need(p, d.head_dim);
-    if (need > 0 && (!workspace || workspace_bytes < need)) {  // one workgroup per row tile
+    // one workgroup per row tile without a workspace, and where a packed batch
+    // has no rows (there is nothing to combine)
+    if (p.splits > 1 && (need == 0 || !workspace || workspace_bytes < need)) {
         p.splits = 1;
         p.split_tiles = 1 << 30;
     } else if (need > 0) {

@@ -1634,7 +1634,7 @@ hipError_t launch_general_norm(const AttnParams& p, int head_dim, hipStream_t st
 
 // The closed-form-mask softmax instantiations of one head dim. D = 64 without
 // score mods or a left bound also with registers for three workgroups per CU
-// (p.wide; 7 registers spill, outside the products). A left-bounded
+// (p.wide; 11 registers spill, outside the products). A left-bounded
 // band (sliding window) checks both bounds on partial tiles.
 template <int D, bool LEFT, bool SPLIT>
 hipError_t launch_closed_form_left(const AttnParams& p, hipStream_t stream)
