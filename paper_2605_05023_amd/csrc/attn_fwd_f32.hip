@@ -429,7 +429,8 @@ __global__ __launch_bounds__(NT, 2) void attn_fwd_f32_kernel(AttnParams p)
 #pragma unroll
         for (int k = 0; k < NW; ++k) {
             const float mk = ml[k][li][0];
-            if (mk != -__builtin_inff()) l_tot += ml[k][li][1] * __builtin_amdgcn_exp2f(mk - m_tot);
+            // (a NaN sum beside m = -inf, every score NaN, must reach l_tot)
+            l_tot += ml[k][li][1] * (mk == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f(mk - m_tot));
         }
         w = m_run == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_tot);
     }

@@ -115,6 +115,27 @@ def test_split_parity(i):
         assert float(np.abs(lg[fin] - lse_ref[fin]).max()) <= LSE_TOL
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("what", ["nan query", "nan key"])
+def test_nan_as_without_a_split(what, dtype):
+    """NaN queries and keys give the NaN that the unsplit call gives."""
+    g = torch.Generator().manual_seed(8)
+    q, k, v = (torch.randn(1, 2, n, 64, generator=g).to(dtype).cuda() for n in (140, 4000, 4000))
+    if what == "nan query":
+        q[0, 1, 7, 3] = float("nan")
+    else:
+        k[0, 1, 2100, 3] = float("nan")
+    kw = dict(mask="none")
+    o, _ = _call(attn.load(), q, k, v, False, kw, True)
+    out, lse = torch.empty_like(q), torch.empty(attn.lse_shape(q, False), device="cuda")
+    d = attn.make_desc(q, k, v, out, **kw)
+    assert attn.load().attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
+                                lse.data_ptr(), ctypes.byref(d)) == 0
+    torch.cuda.synchronize()
+    assert torch.isnan(out).any()
+    assert torch.equal(torch.isnan(o), torch.isnan(out))
+
+
 def test_two_streams_share_nothing():
     """Split calls on two streams, interleaved: each gets the output of the
     same call run alone (every call has a workspace of its own)."""
