@@ -62,7 +62,11 @@ __global__ __launch_bounds__(NT) void attn_combine_kernel(AttnParams p)
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) m_tot = __builtin_fmaxf(m_tot, __shfl_xor(m_tot, d));
     // (m = -inf with a NaN sum: every score was NaN, which must reach the output)
-    const float w = m == -__builtin_inff() && l == 0.0f ? 0.0f : __builtin_amdgcn_exp2f(m - m_tot);
+    // Partials without keys are left out; one whose weight is 0 by underflow is
+    // not, so that an infinite O of it gives the NaN of the unsplit call.
+    const bool empty = m == -__builtin_inff() && l == 0.0f;
+    const float w = empty ? 0.0f : __builtin_amdgcn_exp2f(m - m_tot);
+    const uint64_t used = __builtin_amdgcn_ballot_w64(!empty);
     l *= w;
     lo *= w;
 #pragma unroll
@@ -77,7 +81,7 @@ __global__ __launch_bounds__(NT) void attn_combine_kernel(AttnParams p)
         for (int u = 0; u < BATCH; ++u) {
             const int s = s0 + u * PAR + par;
             const float ws = __shfl(w, s & 63);
-            if (s < p.splits && ws != 0.0f) acc += x[u] * ws;
+            if (s < p.splits && (used >> (s & 63) & 1)) acc += x[u] * ws;
         }
     }
 #pragma unroll

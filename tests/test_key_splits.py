@@ -116,15 +116,21 @@ def test_split_parity(i):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("what", ["nan query", "nan key"])
-def test_nan_as_without_a_split(what, dtype):
-    """NaN queries and keys give the NaN that the unsplit call gives."""
+@pytest.mark.parametrize("what", ["nan query", "nan key", "inf value"])
+def test_nan_and_inf_as_without_a_split(what, dtype):
+    """NaN queries and keys, and an infinite value in a split whose weight
+    underflows, give the NaN that the unsplit call gives."""
     g = torch.Generator().manual_seed(8)
     q, k, v = (torch.randn(1, 2, n, 64, generator=g).to(dtype).cuda() for n in (140, 4000, 4000))
     if what == "nan query":
         q[0, 1, 7, 3] = float("nan")
-    else:
+    elif what == "nan key":
         k[0, 1, 2100, 3] = float("nan")
+    else:  # scores of the first half 800 below the others
+        q[:] = 1.0
+        k[:, :, :2000] = -100.0
+        k[:, :, 2000:] = 0.0
+        v[0, 1, 5, 9] = float("inf")
     kw = dict(mask="none")
     o, _ = _call(attn.load(), q, k, v, False, kw, True)
     out, lse = torch.empty_like(q), torch.empty(attn.lse_shape(q, False), device="cuda")
