@@ -255,7 +255,12 @@ def fwd(q, k, v, *, causal: bool = False, window=None, alibi_slopes=None, softca
                   heads_per_wg=heads_per_wg, order=order, chunk=chunk, log=log)
     # (a negative size is an error that the call itself reports)
     nbytes = lib.attn_workspace_bytes(ctypes.byref(d))
-    ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device) if nbytes > 0 else None
+    ws = None
+    if nbytes > 0:
+        try:
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
+        except torch.OutOfMemoryError:  # computed without the split
+            nbytes = 0
     status = lib.attn_fwd_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
                              lse.data_ptr() if lse is not None else None, ctypes.byref(d),
                              ws.data_ptr() if ws is not None else None, nbytes)

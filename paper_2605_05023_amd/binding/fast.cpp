@@ -258,10 +258,16 @@ bool call(PyObject* const* a, at::Tensor* out, at::Tensor* lse, bool* with_lse)
     const int64_t bytes = g_ws_bytes(&d);
     if (bytes < 0) return false;
     at::Tensor ws;
-    if (bytes > 0) ws = at::empty({bytes}, q.options().dtype(at::kByte));
+    if (bytes > 0) {
+        try {
+            ws = at::empty({bytes}, q.options().dtype(at::kByte));
+        } catch (const c10::OutOfMemoryError&) {
+            // no room for a workspace: the call is computed without the split
+        }
+    }
     return g_fwd_ws(q.const_data_ptr(), k.const_data_ptr(), v.const_data_ptr(), out->mutable_data_ptr(),
                     lse->defined() ? lse->mutable_data_ptr<float>() : nullptr, &d,
-                    bytes > 0 ? ws.mutable_data_ptr() : nullptr, bytes) == ATTN_OK;
+                    ws.defined() ? ws.mutable_data_ptr() : nullptr, ws.defined() ? bytes : 0) == ATTN_OK;
 }
 
 PyObject* py_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)

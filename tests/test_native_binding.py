@@ -77,6 +77,36 @@ def test_given_outputs_come_back():
 
 @gpu
 @needs_gpu
+@pytest.mark.parametrize("path", ["native", "python"])
+def test_no_memory_for_a_workspace(path):
+    """A call whose keys would be split, with no room for the 17 MB workspace, is
+    computed without the split (outputs of bf16: rounding steps apart)."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()  # segments of their own, with no room left in them
+    q, k, v = _x(1, 32, 512, 128), _x(1, 32, 8192, 128), _x(1, 32, 8192, 128, seed=1)
+    kw = dict(validate=True) if path == "python" else {}
+    want, lse_want = attn.fwd(q, k, v)
+    out, lse = torch.empty_like(q), torch.empty(1, 32, 512, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(1e-6)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            torch.empty(17 << 20, dtype=torch.uint8, device="cuda")
+        torch.cuda.reset_peak_memory_stats()
+        held = torch.cuda.memory_allocated()
+        attn.fwd(q, k, v, out=out, lse=lse, **kw)
+        assert torch.cuda.max_memory_allocated() == held  # no workspace
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    torch.cuda.synchronize()
+    # |O| < 0.25 here, where neighbouring bf16 values are 2^-10 apart at most
+    assert float((out.float() - want.float()).abs().max()) <= 2.0 ** -9
+    assert float((lse - lse_want).abs().max()) <= 1e-4
+
+
+@gpu
+@needs_gpu
 def test_refusals_are_those_of_the_python_path():
     q, k, v = _x(1, 4, 20, 64), _x(1, 2, 20, 64), _x(1, 2, 20, 64, seed=1)
     for err, x, kw in [
