@@ -139,7 +139,8 @@ typedef enum attn_status {
 
 /*
  * Problem description. Zero-initialise, set struct_size = sizeof(*desc), then
- * fill the fields. Strides are in elements; 0 selects the contiguous default.
+ * fill the fields. Strides are in elements; 0 selects the contiguous default
+ * (an axis of several entries cannot be broadcast with a stride of 0).
  *
  * Fixed length (cu_seqlens_q == NULL):
  *   q, out [batch, num_q_heads,  seqlen_q, head_dim]

@@ -86,6 +86,12 @@ def lse_shape(q, varlen: bool):
     return (q.shape[1], q.shape[0]) if varlen else (q.shape[0], q.shape[1], q.shape[2])
 
 
+def _broadcast(t):
+    """Is some axis of t expanded (stride 0 over more than one entry)? The
+    descriptor cannot say so: a stride of 0 there selects the contiguous default."""
+    return any(st == 0 and n > 1 for n, st in zip(t.shape, t.stride()))
+
+
 def _check_shapes(q, k, v, out, varlen, alibi_slopes):
     want = 3 if varlen else 4
     layout = "[T, H, D]" if varlen else "[B, H, S, D]"
@@ -96,6 +102,9 @@ def _check_shapes(q, k, v, out, varlen, alibi_slopes):
             raise TypeError(f"{name} is on {t.device}, q on {q.device}")
         if t.stride(-1) != 1:
             raise ValueError("head_dim must be the innermost, contiguous axis")
+        if _broadcast(t):
+            raise ValueError(f"{name} has an expanded axis (stride 0), which the descriptor cannot "
+                             "express")
     if k.shape != v.shape:
         raise ValueError(f"k {tuple(k.shape)} and v {tuple(v.shape)} differ")
     if k.shape[-1] != q.shape[-1]:
@@ -219,6 +228,7 @@ def fwd(q, k, v, *, causal: bool = False, window=None, alibi_slopes=None, softca
     prefix_len, num_global / global_tokens, segment_starts, query_start),
     `relative_position` and `norm` ("softmax", "relu", "sigmoid"; only softmax
     produces an LSE). See make_desc for `validate` and the schedule overrides.
+    Expanded q, k or v (an axis of stride 0) are copied first.
     """
     if not (validate or log or heads_per_wg or order or chunk):
         res = (_native or _load_native()).fwd(
@@ -245,6 +255,8 @@ def fwd(q, k, v, *, causal: bool = False, window=None, alibi_slopes=None, softca
             raise TypeError("lse must be contiguous fp32 on q's device")
         if tuple(lse.shape) != tuple(lse_shape(q, varlen)):
             raise ValueError(f"lse {tuple(lse.shape)} must be {tuple(lse_shape(q, varlen))}")
+    # expanded inputs are laid out in memory (their copies are used on this stream only)
+    q, k, v = (t.contiguous() if _broadcast(t) else t for t in (q, k, v))
     d = make_desc(q, k, v, out, causal=causal, window=window, alibi_slopes=alibi_slopes,
                   softcap=softcap, scale=scale, cu_seqlens_q=cu_seqlens_q,
                   cu_seqlens_k=cu_seqlens_k, max_seqlen_q=max_seqlen_q,

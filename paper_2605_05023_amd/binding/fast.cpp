@@ -46,6 +46,15 @@ bool plain(PyObject* o, at::Tensor* t)
     return !t->key_set().has_any(odd);
 }
 
+// An axis of more than one entry with stride 0 (an expanded tensor): the
+// descriptor takes a stride of 0 for the contiguous default.
+bool broadcast(const at::Tensor& t)
+{
+    for (int64_t i = 0; i < t.dim(); ++i)
+        if (t.stride(i) == 0 && t.size(i) > 1) return true;
+    return false;
+}
+
 bool as_int(PyObject* o, int64_t* v)
 {
     if (!PyLong_CheckExact(o)) return false;
@@ -135,7 +144,8 @@ bool call(PyObject* const* a, at::Tensor* out, at::Tensor* lse, bool* with_lse)
     const bool varlen = a[kCuQ] != Py_None;
     const int64_t rank = varlen ? 3 : 4;
     for (const at::Tensor* t : {&q, &k, &v})
-        if (t->dim() != rank || t->device() != q.device() || t->stride(rank - 1) != 1) return false;
+        if (t->dim() != rank || t->device() != q.device() || t->stride(rank - 1) != 1 || broadcast(*t))
+            return false;
     if (k.sizes() != v.sizes() || k.size(rank - 1) != q.size(rank - 1)) return false;
     if (!varlen && k.size(0) != q.size(0)) return false;
     for (const at::Tensor* t : {&q, &k})
@@ -232,7 +242,7 @@ bool call(PyObject* const* a, at::Tensor* out, at::Tensor* lse, bool* with_lse)
                out->device() != q.device()) {
         return false;
     }
-    if (out->stride(rank - 1) != 1) return false;
+    if (out->stride(rank - 1) != 1 || broadcast(*out)) return false;
     *with_lse = softmax && want_lse;
     if (softmax) {
         const at::DimVector shape = varlen ? at::DimVector{hq, q.size(0)}

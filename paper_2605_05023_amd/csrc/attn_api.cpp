@@ -403,7 +403,7 @@ int check_pointers(const attn_variant_desc& d, const AttnParams& p, const CallSh
     if (!q || !k || !v || !out) return ATTN_ERR_NULL_PTR;
     if (segment_mask(d.mask_kind) && !d.segment_starts) return ATTN_ERR_NULL_PTR;
     {
-        // output rows must not overlap (inputs may: a broadcast K/V is fine)
+        // output rows must not overlap (input rows may)
         const int64_t osize[3] = {varlen ? d.total_q : (int64_t)d.batch, d.num_q_heads,
                                   varlen ? 1 : c.max_q};
         const int64_t ostride[3] = {varlen ? p.so_s : p.so_b, p.so_h, p.so_s};

@@ -90,6 +90,24 @@ def test_innermost_axis_must_be_contiguous():
         desc(fixed(q=q))
 
 
+@pytest.mark.parametrize("name", ["q", "k", "v", "out"])
+def test_expanded_tensors_raise(name):
+    """Stride 0 means the contiguous default in the descriptor: an expanded axis
+    passed through would be read (or written) past the tensor's storage."""
+    shape = fixed()[name].shape
+    for axis in range(3):
+        one = T(*(1 if i == axis else n for i, n in enumerate(shape)))
+        with pytest.raises(ValueError, match="expanded"):
+            desc(fixed(**{name: one.expand(shape)}))
+    shape = packed()[name].shape
+    with pytest.raises(ValueError, match="expanded"):
+        varlen_desc(packed(**{name: T(shape[0], 1, shape[2]).expand(shape)}))
+    # an axis of one entry may have any stride
+    t = fixed(q=T(1, 8, 100, 128), k=T(1, 2, 120, 128), v=T(1, 2, 120, 128), out=T(1, 8, 100, 128))
+    t[name] = t[name][0].expand(t[name].shape)
+    desc(t)
+
+
 PACKED_BAD = [
     ("k head dim", dict(k=T(170, 2, 128), v=T(170, 2, 128))),
     ("k and v tokens", dict(v=T(160, 2, 64))),

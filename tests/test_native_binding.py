@@ -67,6 +67,31 @@ def test_same_outputs_as_the_python_path():
 
 @gpu
 @needs_gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_expanded_inputs_match_their_copies(dtype):
+    """An expanded axis (stride 0) of q, k or v, which the descriptor cannot
+    express: the same outputs as with the copies; an expanded output is refused."""
+    x = dict(dtype=dtype)
+    q, k, v = _x(3, 4, 40, 64, **x), _x(3, 2, 90, 64, **x), _x(3, 2, 90, 64, seed=1, **x)
+    pq, pk, pv = _x(50, 4, 64, **x), _x(50, 1, 64, **x), _x(50, 1, 64, seed=1, **x)
+    cu = dict(cu_seqlens_q=_i32([0, 20, 50]), max_seqlen_q=30, max_seqlen_k=30)
+    for (a, b, c), kw in [
+        ((q, k[:1].expand(3, -1, -1, -1), v[:1].expand(3, -1, -1, -1)), {}),
+        ((q, k[:, :1].expand(-1, 4, -1, -1), v[:, 1:].expand(-1, 4, -1, -1)), {}),
+        ((q, k, v[:, :, :1].expand(-1, -1, 90, -1)), {}),
+        ((q[:1, :1].expand(3, 4, -1, -1), k, v), {}),
+        ((pq, pk.expand(-1, 2, -1), pv.expand(-1, 2, -1)), cu),
+    ]:
+        want = attn.fwd(*(t.contiguous() for t in (a, b, c)), causal=True, **kw)
+        got = attn.fwd(a, b, c, causal=True, **kw)
+        torch.cuda.synchronize()
+        assert all(torch.equal(g, w) for g, w in zip(got, want))
+    with pytest.raises(ValueError, match="expanded"):
+        attn.fwd(q, k, v, out=torch.empty_like(q[:, :1]).expand(-1, 4, -1, -1))
+
+
+@gpu
+@needs_gpu
 def test_given_outputs_come_back():
     q, k, v = _x(1, 2, 20, 64), _x(1, 2, 20, 64), _x(1, 2, 20, 64, seed=1)
     out, lse = torch.empty_like(q), torch.empty(1, 2, 20, device="cuda")
