@@ -99,6 +99,10 @@ typedef enum attn_dtype {
  *                    j <= i' and either i' >= query_start or i' and j lie in
  *                    the same document (Appendix A "Causal Blockwise Mask").
  * A row with no visible key gets O = 0 and (softmax) LSE = -inf.
+ * Infinite and NaN values: with fp32 inputs a key that a row does not see leaves
+ * the row's output alone, whatever its K and V hold. With bf16 inputs an infinite
+ * or NaN V row may make rows NaN that do not see its key but share a tile of 64
+ * keys and up to 128 rows with one that does.
  */
 typedef enum attn_mask_kind {
     ATTN_MASK_NONE = 0,

@@ -57,6 +57,59 @@ def test_tile_edges(d, lq, lk, mask):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("what", ["causal", "window", "prefix_lm", "share_question", "listed global",
+                                  "relu", "sigmoid split", "gathered past the band"])
+def test_values_of_unseen_keys_stay_out(what, d):
+    """Infinite and NaN values reach the rows that see their key, and no other
+    row of the 32-row block: those are bit for bit what zeros in their place
+    give (a product with P = 0 would make them NaN)."""
+    lq, lk = (150, 1700) if what == "sigmoid split" else (97, 161)
+    g = torch.Generator().manual_seed(d + len(what))
+    q = torch.randn(1, 2, lq, d, generator=g)
+    k, v = (torch.randn(1, 1, lk, d, generator=g) for _ in range(2))
+    bad = {lk - 1: float("inf"), lk - 30: float("nan"), lk - 70: float("-inf"), 3: float("inf"),
+           70: float("nan")}
+    dims = {j: (7 * n + 1) % d for n, j in enumerate(bad)}
+    v_bad, v_zero = v.clone(), v.clone()
+    for j, x in bad.items():
+        v_bad[0, 0, j, dims[j]], v_zero[0, 0, j, dims[j]] = x, 0.0
+    v_bad[0, 0, 3, dims[lk - 30]], v_zero[0, 0, 3, dims[lk - 30]] = float("-inf"), 0.0
+    i, j = np.arange(lq)[:, None] + (lk - lq), np.arange(lk)[None, :]
+    causal, kw = j <= i, dict(causal=True)
+    seen = causal
+    if what == "window":
+        seen, kw = (i - j <= 40) & (j - i <= 3), dict(window=(40, 3))
+    elif what == "prefix_lm":
+        seen, kw = causal | (j < 50), dict(mask="prefix_lm", prefix_len=50)
+    elif what == "share_question":
+        starts = np.array([20, 90, 130])
+        seg = lambda t: np.searchsorted(starts, t, side="right")
+        seen = causal & ((seg(j) == 0) | (seg(i) == seg(j)))
+        kw = dict(mask="share_question", segment_starts=torch.tensor(starts, dtype=torch.int32).cuda())
+    elif what in ("listed global", "gathered past the band"):
+        tok = [3, 70, 100] if what == "listed global" else [5, lk - 30, lk - 1]
+        w = (40, 3) if what == "listed global" else (10, 0)
+        seen = ((i - j <= w[0]) & (j - i <= w[1])) | np.isin(i, tok) | np.isin(j, tok)
+        kw = dict(mask="global_sliding_window", window=w,
+                  global_tokens=torch.tensor(tok, dtype=torch.int32).cuda())
+    elif what != "causal":
+        kw["norm"] = what.split()[0]
+    got, want = (fwd(q.cuda(), k.cuda(), x.cuda(), return_lse=False, **kw).cpu() for x in (v_bad, v_zero))
+    hit = np.zeros((lq, d), bool)
+    for key in bad:
+        hit[seen[:, key], dims[key]] = True
+    hit[seen[:, 3], dims[lk - 30]] = True
+    hit = torch.from_numpy(hit).expand(1, 2, -1, -1)
+    assert hit.any() and not hit.all()
+    assert torch.equal(got[~hit], want[~hit])
+    assert not torch.isfinite(got[hit]).any()
+    if what == "causal":  # one infinite key seen: its infinity; none of these rows sees two
+        only = hit.clone()
+        only[..., [x for n, x in dims.items() if n != lk - 1]] = False
+        assert torch.isinf(got[only]).all() and (got[only] > 0).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_one_key_of_small_row_stride(d):
     """A single key row may have any row stride; the rows past it stay zero."""
     g = torch.Generator().manual_seed(d)
