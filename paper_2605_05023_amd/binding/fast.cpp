@@ -121,6 +121,11 @@ bool layout_array(const at::Tensor& t, const at::Tensor& q, int64_t nseq, int64_
     return true;
 }
 
+struct NoGil {
+    PyThreadState* state = PyEval_SaveThread();
+    ~NoGil() { PyEval_RestoreThread(state); }
+};
+
 enum Arg {
     kQ, kK, kV, kCausal, kWindow, kSlopes, kSoftcap, kScale, kCuQ, kCuK, kMaxQ, kMaxK, kOut, kLse,
     kReturnLse, kMask, kPrefix, kNumGlobal, kGlobalTokens, kSegments, kQueryStart, kRelPos, kNorm,
@@ -234,26 +239,25 @@ bool call(PyObject* const* a, at::Tensor* out, at::Tensor* lse, bool* with_lse)
         d.global_tokens = n ? glob.const_data_ptr<int32_t>() : nullptr;
     }
 
+    if (a[kOut] != Py_None && (!plain(a[kOut], out) || out->scalar_type() != dt ||
+                               out->sizes() != q.sizes() || out->device() != q.device()))
+        return false;
+    *with_lse = softmax && want_lse;
+    const at::DimVector shape = varlen ? at::DimVector{hq, q.size(0)}
+                                       : at::DimVector{q.size(0), hq, q.size(2)};
+    if (softmax && a[kLse] != Py_None &&
+        (!plain(a[kLse], lse) || lse->scalar_type() != at::kFloat || !lse->is_contiguous() ||
+         lse->device() != q.device() || lse->sizes() != at::IntArrayRef(shape)))
+        return false;
+
+    // From here on no Python object is touched: other threads run meanwhile (an
+    // allocation or a launch can wait for the GPU).
+    const NoGil nogil;
     // outputs and workspace (kernel outputs take no part in autograd)
     at::AutoDispatchBelowADInplaceOrView below;
-    if (a[kOut] == Py_None) {
-        *out = at::empty_like(q);
-    } else if (!plain(a[kOut], out) || out->scalar_type() != dt || out->sizes() != q.sizes() ||
-               out->device() != q.device()) {
-        return false;
-    }
+    if (!out->defined()) *out = at::empty_like(q);
     if (out->stride(rank - 1) != 1 || broadcast(*out)) return false;
-    *with_lse = softmax && want_lse;
-    if (softmax) {
-        const at::DimVector shape = varlen ? at::DimVector{hq, q.size(0)}
-                                           : at::DimVector{q.size(0), hq, q.size(2)};
-        if (a[kLse] == Py_None) {
-            if (want_lse) *lse = at::empty(shape, q.options().dtype(at::kFloat));
-        } else if (!plain(a[kLse], lse) || lse->scalar_type() != at::kFloat || !lse->is_contiguous() ||
-                   lse->device() != q.device() || lse->sizes() != at::IntArrayRef(shape)) {
-            return false;
-        }
-    }
+    if (*with_lse && !lse->defined()) *lse = at::empty(shape, q.options().dtype(at::kFloat));
     const int64_t sb = varlen ? -1 : 0, ss = varlen ? 0 : 2;  // axes of the batch and token strides
     auto strides = [&](const at::Tensor& t, int64_t* b, int64_t* h, int64_t* s) {
         if (sb >= 0) *b = t.stride(sb);

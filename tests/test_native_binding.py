@@ -2,6 +2,10 @@
 the same descriptor (the launch plan printed by the log flag apart, which only
 the Python path takes), the same outputs bit for bit, and the same refusals.
 """
+import ctypes
+import subprocess
+import threading
+
 import pytest
 import torch
 
@@ -171,3 +175,52 @@ def test_subclasses_and_modes_take_the_python_path():
     o = torch.empty(20, 64)
     assert torch.func.vmap(lambda t: o if native.fwd(t, t, t, *args) is NotImplemented else t[0, 0])(
         torch.stack([q, q])).shape == (2, 20, 64)
+
+
+@gpu
+@needs_gpu
+def test_other_threads_run_during_a_call(tmp_path):
+    """The native path gives up the interpreter lock for the call into the
+    library: in its place a function that waits (3 s at most) until another
+    Python thread has seen it start."""
+    src = tmp_path / "wait.c"
+    src.write_text("""
+        #include <time.h>
+        volatile int started, answered, in_time;
+        int wait_fwd(void *q, void *k, void *v, void *o, float *l, void *d, void *w, long long n)
+        {
+            struct timespec a, b;
+            clock_gettime(CLOCK_MONOTONIC, &a);
+            started = 1;
+            do clock_gettime(CLOCK_MONOTONIC, &b);
+            while (!answered && b.tv_sec - a.tv_sec < 3);
+            in_time = answered;
+            return 0;
+        }
+        long long no_bytes(void *d) { return 0; }
+        """)
+    so = tmp_path / "wait.so"
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", str(src), "-o", str(so)], check=True)
+    lib = ctypes.CDLL(str(so))
+    started, answered = (ctypes.c_int.in_dll(lib, n) for n in ("started", "answered"))
+    done = threading.Event()
+
+    def answer():
+        while not started.value and not done.is_set():
+            done.wait(0.001)
+        if not done.is_set():
+            answered.value = 1
+
+    native = attn._load_native()
+    q, k, v = _x(1, 2, 20, 64), _x(1, 2, 20, 64), _x(1, 2, 20, 64, seed=1)
+    native.bind(ctypes.cast(lib.wait_fwd, ctypes.c_void_p).value,
+                ctypes.cast(lib.no_bytes, ctypes.c_void_p).value)
+    t = threading.Thread(target=answer)
+    try:
+        t.start()
+        attn.fwd(q, k, v)
+    finally:
+        done.set()
+        t.join()
+        attn._load_native()
+    assert ctypes.c_int.in_dll(lib, "in_time").value == 1
