@@ -233,7 +233,8 @@ typedef struct attn_variant_desc {
  *   lse     : device fp32 output (layout above), or NULL to skip it; only
  *             written for the softmax normalisation
  * Returns ATTN_OK once the kernel is enqueued (it runs asynchronously), or an
- * error code; on error nothing was enqueued. A zero-sized problem (batch,
+ * error code; on error nothing was enqueued (of a call with two kernels, see
+ * attn_fwd_ws, the first may have been when ATTN_ERR_LAUNCH is returned). A zero-sized problem (batch,
  * seqlen or total of 0) enqueues nothing and returns ATTN_OK.
  */
 int attn_fwd(const void *q, const void *k, const void *v, void *out, float *lse,
@@ -249,7 +250,9 @@ int attn_fwd(const void *q, const void *k, const void *v, void *out, float *lse,
  * call); the results agree to rounding. The workspace needs 16-byte alignment
  * (ATTN_ERR_ALIGNMENT otherwise) and no initialisation, holds nothing between
  * calls, and must stay valid, and unused by other streams, until the work on
- * desc->stream has completed.
+ * desc->stream has completed. That holds after ATTN_ERR_LAUNCH too, and for
+ * every other buffer of the call: the first kernel may be running when the
+ * launch of the second fails.
  */
 int64_t attn_workspace_bytes(const attn_variant_desc *desc);
 int attn_fwd_ws(const void *q, const void *k, const void *v, void *out, float *lse,

@@ -13,7 +13,8 @@
 // arguments of the expected types, no schedule override, no validation or log.
 // Everything it does not take (anything it would have to report as an error
 // included) returns NotImplemented before any work, and the Python path of
-// fwd, which raises the errors, runs instead. No arithmetic is done here.
+// fwd, which raises the errors, runs instead. A launch that fails is raised
+// here: the call is not made a second time. No arithmetic is done here.
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <Python.h>
@@ -132,9 +133,9 @@ enum Arg {
     kArgs
 };
 
-// True with the outputs set when the call was made; false when the Python path
-// has to take it.
-bool call(PyObject* const* a, at::Tensor* out, at::Tensor* lse, bool* with_lse)
+// True with the outputs and the library's status set when the call was made;
+// false when the Python path has to take it.
+bool call(PyObject* const* a, at::Tensor* out, at::Tensor* lse, bool* with_lse, int* status)
 {
     at::Tensor q, k, v;
     if (!plain(a[kQ], &q) || !plain(a[kK], &k) || !plain(a[kV], &v)) return false;
@@ -279,9 +280,12 @@ bool call(PyObject* const* a, at::Tensor* out, at::Tensor* lse, bool* with_lse)
             // no room for a workspace: the call is computed without the split
         }
     }
-    return g_fwd_ws(q.const_data_ptr(), k.const_data_ptr(), v.const_data_ptr(), out->mutable_data_ptr(),
-                    lse->defined() ? lse->mutable_data_ptr<float>() : nullptr, &d,
-                    ws.defined() ? ws.mutable_data_ptr() : nullptr, ws.defined() ? bytes : 0) == ATTN_OK;
+    *status = g_fwd_ws(q.const_data_ptr(), k.const_data_ptr(), v.const_data_ptr(),
+                       out->mutable_data_ptr(),
+                       lse->defined() ? lse->mutable_data_ptr<float>() : nullptr, &d,
+                       ws.defined() ? ws.mutable_data_ptr() : nullptr, ws.defined() ? bytes : 0);
+    // every other status is a refusal of the arguments, before any launch
+    return *status == ATTN_OK || *status == ATTN_ERR_LAUNCH;
 }
 
 PyObject* py_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
@@ -293,7 +297,14 @@ PyObject* py_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     try {
         at::Tensor out, lse;
         bool with_lse = false;
-        if (!g_fwd_ws || !call(a, &out, &lse, &with_lse)) Py_RETURN_NOTIMPLEMENTED;
+        int status = ATTN_OK;
+        if (!g_fwd_ws || !call(a, &out, &lse, &with_lse, &status)) Py_RETURN_NOTIMPLEMENTED;
+        if (status != ATTN_OK) {  // raises AttnError
+            PyObject* abi = PyImport_ImportModule("paper_2605_05023_amd._abi");
+            PyObject* none = abi ? PyObject_CallMethod(abi, "check", "i", status) : nullptr;
+            Py_XDECREF(abi);
+            return none;
+        }
         PyObject* o = a[kOut] == Py_None ? THPVariable_Wrap(out) : Py_NewRef(a[kOut]);
         if (!o || !with_lse) return o;
         PyObject* l = a[kLse] == Py_None ? THPVariable_Wrap(lse) : Py_NewRef(a[kLse]);

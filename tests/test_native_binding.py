@@ -224,3 +224,26 @@ def test_other_threads_run_during_a_call(tmp_path):
         t.join()
         attn._load_native()
     assert ctypes.c_int.in_dll(lib, "in_time").value == 1
+
+
+@gpu
+@needs_gpu
+def test_a_failed_launch_is_raised_once():
+    """ATTN_ERR_LAUNCH comes back as AttnError from the call that got it; the
+    call is not repeated through the Python path."""
+    native = attn._load_native()
+    q, k, v = _x(1, 2, 20, 64), _x(1, 2, 20, 64), _x(1, 2, 20, 64, seed=1)
+    calls = []
+    failing = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_void_p] * 7, ctypes.c_int64)(
+        lambda *a: calls.append(1) or -7)
+    native.bind(ctypes.cast(failing, ctypes.c_void_p).value,
+                ctypes.cast(attn.load().attn_workspace_bytes, ctypes.c_void_p).value)
+    try:
+        with pytest.raises(attn.AttnError) as e:
+            attn.fwd(q, k, v)
+    finally:
+        attn._load_native()
+    assert e.value.status == -7 and len(calls) == 1
+    o, _ = attn.fwd(q, k, v)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o.float()).all()
