@@ -34,7 +34,8 @@ __global__ __launch_bounds__(NT) void attn_combine_kernel(AttnParams p)
     const bool varlen = p.cu_q != nullptr;
     const int64_t per_head = varlen ? p.total_q : p.seqlen_q;
     const int64_t bh = row / per_head, i = row - bh * per_head;
-    if (varlen && i >= p.cu_q[p.batch]) return;  // a token of no sequence: nothing was computed
+    // a token of no sequence: nothing was computed, its output stays as it is
+    if (varlen && (i < p.cu_q[0] || i >= p.cu_q[p.batch])) return;
     const int64_t b = varlen ? 0 : bh / p.hq, h = bh - b * p.hq;
 
     // The O pieces of the first BATCH splits are requested beside the scalars

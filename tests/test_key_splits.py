@@ -142,6 +142,29 @@ def test_nan_and_inf_as_without_a_split(what, dtype):
     assert torch.equal(torch.isnan(o), torch.isnan(out))
 
 
+@pytest.mark.parametrize("dtype,lq", [("bf16", 1), ("bf16", 150), ("fp32", 40)])
+def test_rows_of_no_sequence_stay_as_they_are(dtype, lq):
+    """A packed call writes the rows of its sequences: tokens before the first
+    and past the last one keep what out and lse held."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(lq)
+    hq, lk, pre, post = 2, 4000, 5, 3
+    q = torch.randn(pre + lq + post, hq, 128, generator=g).to(tdt).cuda()
+    k, v = (torch.randn(lk, hq, 128, generator=g).to(tdt).cuda() for _ in range(2))
+    cu = [torch.tensor(x, dtype=torch.int32, device="cuda") for x in ([pre, pre + lq], [0, lk])]
+    kw = dict(causal=True, cu_seqlens_q=cu[0], cu_seqlens_k=cu[1], max_seqlen_q=lq, max_seqlen_k=lk)
+    out, lse = torch.full_like(q, 7.0), torch.full((hq, q.shape[0]), 7.0, device="cuda")
+    d = attn.make_desc(q, k, v, out, **kw)
+    assert attn.load().attn_workspace_bytes(ctypes.byref(d)) > 0
+    attn.fwd(q, k, v, out=out, lse=lse, **kw)
+    kw["cu_seqlens_q"] = torch.tensor([0, lq], dtype=torch.int32, device="cuda")
+    want, lse_want = attn.fwd(q[pre:pre + lq].contiguous(), k, v, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(out[pre:pre + lq], want) and torch.equal(lse[:, pre:pre + lq], lse_want)
+    for s in (slice(0, pre), slice(pre + lq, None)):
+        assert (out[s] == 7.0).all() and (lse[:, s] == 7.0).all()
+
+
 def test_two_streams_share_nothing():
     """Split calls on two streams, interleaved: each gets the output of the
     same call run alone (every call has a workspace of its own)."""
