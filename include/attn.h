@@ -245,7 +245,8 @@ int attn_fwd(const void *q, const void *k, const void *v, void *out, float *lse,
  * query rows to fill the GPU, the keys of each row are split over workgroups,
  * which leave partial results in the workspace for a second, small kernel on
  * the same stream. attn_workspace_bytes returns the bytes the call described
- * by `desc` can use (0: none; negative: an attn_status_t). With a NULL or
+ * by `desc` can use (0: none; negative: an attn_status_t): no more than a quarter
+ * of the bytes of q, k, v and out, or 64 MiB where that is more. With a NULL or
  * smaller workspace the call is computed without the split (attn_fwd is that
  * call); the results agree to rounding. The workspace needs 16-byte alignment
  * (ATTN_ERR_ALIGNMENT otherwise) and no initialisation, holds nothing between

@@ -428,6 +428,40 @@ int64_t max_key_tiles(const AttnParams& p, int64_t max_k, int64_t span, int64_t 
     return (keys + bn - 1) / bn;
 }
 
+int64_t workspace_need(const AttnParams& p, int64_t D)
+{
+    if (p.splits <= 1) return 0;
+    return p.parts * (D + 4) * 4 + (p.cu_q ? p.ws_rows * 8 : 0);
+}
+
+// Largest workspace of a call that moves `io` bytes of inputs and outputs.
+// Calls of even lengths need 35 MB at most (a split is made where there are
+// fewer workgroups than CUs); an uneven packed batch with many query rows could
+// ask for any amount, and coarser splits serve it nearly as well.
+int64_t workspace_limit(int64_t io) { return io / 4 > (int64_t)64 << 20 ? io / 4 : (int64_t)64 << 20; }
+
+// Split row tiles of up to max_tiles tiles of `bn` keys every `per` tiles, or
+// more where the partial results would take more than `limit` bytes. (A packed
+// batch without rows has nothing to combine.)
+void set_splits(AttnParams& p, int64_t D, int64_t bn, int64_t max_tiles, int64_t per, int64_t limit)
+{
+    for (; p.ws_rows > 0 && per < max_tiles; per *= 2) {
+        p.splits = (int32_t)((max_tiles + per - 1) / per);
+        p.split_tiles = (int32_t)per;
+        p.part_stride = p.ws_rows;
+        p.parts = p.splits * p.ws_rows;
+        if (p.cu_q) {
+            const int64_t half = per * bn / 2;
+            p.part_stride = (int64_t)p.hq * p.max_q;
+            p.parts = p.total_k / half * p.part_stride;
+            p.div_part = make_fastdiv((uint32_t)half);
+        }
+        if (p.parts > 0 && p.parts <= INT32_MAX && workspace_need(p, D) <= limit) return;
+    }
+    p.splits = 1;
+    p.split_tiles = 1 << 30;
+}
+
 // Key splits of the decode kernel for `units` row tiles of max_tiles key tiles
 // at most and avg_tiles on average. A split and its combining launch cost about
 // 2.5 us, so up to 512 keys stay whole (300 keys: 6.7 us whole, 9.0 split).
@@ -439,7 +473,8 @@ int64_t max_key_tiles(const AttnParams& p, int64_t max_k, int64_t span, int64_t 
 // length are cut into eight times as many pieces, so that the longest do not
 // outlast the rest (32 of 256..8192 keys: 138 us with 256 pieces aimed at, 119
 // with 1024, 116 with 2048).
-void split_decode(AttnParams& p, bool packed, int64_t units, int64_t max_tiles, int64_t avg_tiles)
+void split_decode(AttnParams& p, int64_t D, bool packed, int64_t units, int64_t max_tiles,
+                  int64_t avg_tiles, int64_t limit)
 {
     if (max_tiles <= 16) return;
     const int64_t pieces = packed ? 2048 : 256;
@@ -450,10 +485,7 @@ void split_decode(AttnParams& p, bool packed, int64_t units, int64_t max_tiles, 
     if (least < floor_splits) least = floor_splits;
     if (per < least) per = least;
     per = (per + 3) / 4 * 4;  // whole rounds of the four waves
-    const int64_t splits = (max_tiles + per - 1) / per;
-    if (splits <= 1) return;
-    p.splits = (int32_t)splits;
-    p.split_tiles = (int32_t)per;
+    set_splits(p, D, attn::decode_keys(), max_tiles, per, limit);
 }
 
 // Key splits of the prefill and fp32 kernels for `items` workgroups with rows,
@@ -467,8 +499,8 @@ void split_decode(AttnParams& p, bool packed, int64_t units, int64_t max_tiles, 
 // queries, 4096 keys, D = 64: 45 and 20; 16 heads of 2048 causal rows (256
 // workgroups): 37 whole, 50 in splits of 16 tiles. fp32, 8 heads, one query,
 // 4000 keys: 133 and 17.
-void split_underfilled(AttnParams& p, int64_t D, int64_t items, int64_t max_tiles, int64_t avg_tiles,
-                       int64_t rows, int64_t least, double tile_us)
+void split_underfilled(AttnParams& p, int64_t D, int64_t bn, int64_t items, int64_t max_tiles,
+                       int64_t avg_tiles, int64_t least, double tile_us, int64_t limit)
 {
     if (avg_tiles > max_tiles) avg_tiles = max_tiles;
     if (avg_tiles < 1) return;
@@ -481,10 +513,9 @@ void split_underfilled(AttnParams& p, int64_t D, int64_t items, int64_t max_tile
     int64_t usual = avg_tiles / per + 1;  // splits of the usual row
     if (usual > splits) usual = splits;
     const double saved = (double)(max_tiles - per) * tile_us;
-    const double cost = 5.0 + (double)(rows * usual) * (double)(D + 4) * 8.0 / 2.5e6;
+    const double cost = 5.0 + (double)(p.ws_rows * usual) * (double)(D + 4) * 8.0 / 2.5e6;
     if (saved < 1.33 * cost) return;
-    p.splits = (int32_t)splits;
-    p.split_tiles = (int32_t)per;
+    set_splits(p, D, bn, max_tiles, per, limit);
 }
 
 // Everything the kernels take but the data pointers: schedule and score
@@ -665,6 +696,10 @@ int plan_launch(const attn_variant_desc& d, AttnParams& p, const CallShape& c)
     p.split_tiles = 1 << 30;
     p.ws_rows = varlen ? (int64_t)d.num_q_heads * d.total_q
                        : (int64_t)d.batch * d.num_q_heads * d.seqlen_q;
+    p.max_q = (int32_t)max_q;
+    p.total_k = varlen ? d.total_k : 0;
+    const int64_t keys = varlen ? d.total_k : (int64_t)d.batch * d.seqlen_k;
+    const int64_t limit = workspace_limit((p.ws_rows + keys * d.num_kv_heads) * 2 * D * elt);
     // Few query rows per kv head: the decode kernel (schedule overrides keep
     // the prefill kernel that they describe).
     const int64_t groups = (int64_t)d.batch * d.num_kv_heads;
@@ -678,8 +713,8 @@ int plan_launch(const attn_variant_desc& d, AttnParams& p, const CallShape& c)
         p.div_group = make_fastdiv((uint32_t)group);
         const int64_t bn = attn::decode_keys();
         const int64_t avg_k = varlen ? d.total_k / d.batch : d.seqlen_k;
-        split_decode(p, varlen, groups * rt, max_key_tiles(p, c.max_k, max_q, bn),
-                     (avg_k + bn - 1) / bn);
+        split_decode(p, D, varlen, groups * rt, max_key_tiles(p, c.max_k, max_q, bn),
+                     (avg_k + bn - 1) / bn, limit);
         p.grid = (int32_t)(groups * rt);
     } else if (!scheduled && !p.gtok) {
         const bool bf16 = d.dtype == ATTN_BF16;
@@ -691,15 +726,10 @@ int plan_launch(const attn_variant_desc& d, AttnParams& p, const CallShape& c)
         // causal-like masks: the average row sees usual_k - usual_q / 2 keys
         const int64_t seen = d.mask_kind == ATTN_MASK_NONE ? usual_k : usual_k - usual_q / 2;
         const double tile_us = (D == 128 ? 0.85 : 0.5) * (bf16 ? 1.0 : 1.2);
-        split_underfilled(p, D, items, max_key_tiles(p, c.max_k, block_m, bn), (seen + bn - 1) / bn,
-                          p.ws_rows, bf16 ? 8 : 4, tile_us);
+        split_underfilled(p, D, bn, items, max_key_tiles(p, c.max_k, block_m, bn), (seen + bn - 1) / bn,
+                          bf16 ? 8 : 4, tile_us, limit);
     }
     return ATTN_OK;
-}
-
-int64_t workspace_need(const AttnParams& p, int64_t D)
-{
-    return p.splits > 1 ? p.splits * p.ws_rows * (D + 4) * 4 : 0;
 }
 
 }  // namespace
@@ -743,14 +773,13 @@ extern "C" int attn_fwd_ws(const void* q, const void* k, const void* v, void* ou
     p.o = out;
     p.lse = lse;
     const int64_t need = workspace_need(p, d.head_dim);
-    // one workgroup per row tile without a workspace, and where a packed batch
-    // has no rows (there is nothing to combine)
-    if (p.splits > 1 && (need == 0 || !workspace || workspace_bytes < need)) {
+    if (need > 0 && (!workspace || workspace_bytes < need)) {  // one workgroup per row tile
         p.splits = 1;
         p.split_tiles = 1 << 30;
     } else if (need > 0) {
         p.ws_o = static_cast<float*>(workspace);
-        p.ws_ml = p.ws_o + p.splits * p.ws_rows * d.head_dim;
+        p.ws_ml = p.ws_o + p.parts * d.head_dim;
+        p.ws_mark = reinterpret_cast<int32_t*>(p.ws_ml + p.parts * 4);
     }
     if (d.flags & ATTN_FLAG_VALIDATE) {
         rc = validate_device_inputs(d, p.cu_q != nullptr, p.seg != nullptr, p.gtok != nullptr);

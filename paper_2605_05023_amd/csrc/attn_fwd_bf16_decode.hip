@@ -104,10 +104,8 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
     const int q0 = (int)fast_div((uint32_t)f0, p.div_group);
     const int q1 = (int)fast_div((uint32_t)min(f0 + kRows, nflat) - 1u, p.div_group);
     const TilePlan gp = plan_tiles(p.band, q0, q1 - q0 + 1, lq, lk, kBn);
-    const int t_beg = gp.lo + (int)sp * p.split_tiles;
-    // (the last split takes whatever is left, so every tile has its split even
-    // where a sequence is longer than the host was told)
-    const int t_end = (int)sp == p.splits - 1 ? gp.hi : min(gp.hi, t_beg + p.split_tiles);
+    int t_beg = gp.lo, t_end = gp.hi;
+    const bool partial = split_share(p, (int)sp, splittable(p, lq, krow0, lk), t_beg, t_end);
 
     WaveState<T> ws;
     ws.lh = lh;
@@ -124,13 +122,10 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
         if (p.relpos) ws.bias_lin = p.unit;
     }
     const float lse_shift = ws.bias_lin != 0.0f ? (float)(ws.ip - ws.jref) : 0.0f;
-    float* ws_ml = p.ws_ml + ((int64_t)sp * p.ws_rows + row) * 4;
-    // a row tile with no more key tiles than one split takes is written by its
-    // first split as if it were not split
-    const bool partial = gp.hi - gp.lo > p.split_tiles;
     if (sp > 0 && t_beg >= t_end) {  // no tiles: an empty partial
-        if (wave == 0 && lh == 0 && row_ok)
-            *reinterpret_cast<f32x4*>(ws_ml) = f32x4{-__builtin_inff(), 0.0f, 0.0f, lse_shift};
+        if (partial && !p.cu_q && wave == 0 && lh == 0 && row_ok)
+            *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.part_stride + row) * 4) =
+                f32x4{-__builtin_inff(), 0.0f, 0.0f, lse_shift};
         return;
     }
 
@@ -265,7 +260,8 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
     const float inv = l_tot > 0.0f && lo_tot > 0.0f ? 1.0f / lo_tot : 0.0f;
     __bf16* orow = static_cast<__bf16*>(p.o) + (int64_t)hq * p.so_h +
                    (p.cu_q ? qrow0 + qi : qi) * p.so_s + (p.cu_q ? 0 : b * p.so_b);
-    float* prow = p.ws_o + ((int64_t)sp * p.ws_rows + row) * D;
+    const int64_t part = part_index(p, row, krow0, hq, qi), prt = part + sp * p.part_stride;
+    float* prow = p.ws_o + prt * D;
 #pragma unroll
     for (int i0 = 0; i0 < T::DBLK; i0 += 2) {
         const int i = wave * T::DBLK + i0;  // pieces i and i + 1 hold eight consecutive dims
@@ -286,9 +282,8 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
         }
     }
     if (wave == 0 && lh == 0) {
-        if (p.splits > 1)
-            *reinterpret_cast<f32x4*>(ws_ml) =
-                partial ? f32x4{m_tot, l_tot, lo_tot, lse_shift} : f32x4{0.0f, 0.0f, -1.0f, 0.0f};
+        if (partial) *reinterpret_cast<f32x4*>(p.ws_ml + prt * 4) = f32x4{m_tot, l_tot, lo_tot, lse_shift};
+        if (p.splits > 1 && sp == 0) mark_row(p, row, partial, part, gp.hi - gp.lo);
         if (!partial && p.lse)
             p.lse[row] = l_tot > 0.0f ? (m_tot + __builtin_log2f(l_tot)) * kLn2 + lse_shift
                                       : -__builtin_inff();

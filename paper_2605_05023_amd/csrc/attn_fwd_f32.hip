@@ -40,6 +40,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "key_splits.h"
 #include "kernel_params.h"
 #include "launch.h"
 #include "row_vis.h"
@@ -202,18 +203,16 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void attn_fwd_f32_kernel(AttnP
         t_lo = gp.lo;
         t_hi = gp.hi;
     }
-    // This split's share of the tiles. A row tile with no more key tiles than
-    // one split takes is written by its first split as if it were not split.
+    // This split's share of the tiles.
     const int64_t row = p.cu_q ? (int64_t)hq * p.total_q + qrow0 + qi
                                : ((int64_t)b * p.hq + hq) * lq + qi;  // index of its LSE
     bool partial = false;
+    const int tiles = t_hi - t_lo;
     if (p.splits > 1) {
-        partial = t_hi - t_lo > p.split_tiles;
-        t_lo += (int)sp * p.split_tiles;
-        if ((int)sp < p.splits - 1) t_hi = min(t_hi, t_lo + p.split_tiles);
+        partial = split_share(p, (int)sp, splittable(p, lq, krow0, lk), t_lo, t_hi);
         if (sp > 0 && t_lo >= t_hi) {  // no tiles: an empty partial
-            if (wave == 0 && lh == 0 && qi < lq)
-                *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.ws_rows + row) * 4) =
+            if (partial && !p.cu_q && wave == 0 && lh == 0 && qi < lq)
+                *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.part_stride + row) * 4) =
                     f32x4{-__builtin_inff(), 0.0f, 0.0f, 0.0f};
             return;
         }
@@ -505,8 +504,9 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void attn_fwd_f32_kernel(AttnP
     else
         inv = lk > 0 ? 1.0f / (float)lk : 0.0f;
     float* dst = ob + ooff + (int64_t)qi * p.so_s + DB * (8 * wave + 4 * lh);
+    const int64_t first = part_index(p, row, krow0, hq, qi), prt = first + sp * p.part_stride;
     if (partial) {  // unnormalised O (ReLU, Sigmoid: the share of O)
-        dst = p.ws_o + (sp * p.ws_rows + row) * D + DB * (8 * wave + 4 * lh);
+        dst = p.ws_o + prt * D + DB * (8 * wave + 4 * lh);
         if (SOFTMAX) inv = 1.0f;
     }
 #pragma unroll
@@ -516,11 +516,11 @@ __global__ __launch_bounds__(NT, D == 64 ? 3 : 2) void attn_fwd_f32_kernel(AttnP
         *reinterpret_cast<vrow_t*>(dst + DB * e) = x * inv;
     }
     if (p.splits > 1 && wave == 0 && lh == 0) {
-        f32x4 sc = {0.0f, 0.0f, -1.0f, 0.0f};  // written here: nothing to combine
         if (partial)
-            sc = SOFTMAX ? f32x4{m_tot, l_tot, l_tot, bias_lin != 0.0f ? (float)(ip - jref) : 0.0f}
-                         : f32x4{0.0f, 1.0f, 1.0f, 0.0f};
-        *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.ws_rows + row) * 4) = sc;
+            *reinterpret_cast<f32x4*>(p.ws_ml + prt * 4) =
+                SOFTMAX ? f32x4{m_tot, l_tot, l_tot, bias_lin != 0.0f ? (float)(ip - jref) : 0.0f}
+                        : f32x4{0.0f, 1.0f, 1.0f, 0.0f};
+        if (sp == 0) mark_row(p, row, partial, first, tiles);
     }
     if (SOFTMAX && !partial && p.lse && wave == 0 && lh == 0) {
         float lse = -__builtin_inff();

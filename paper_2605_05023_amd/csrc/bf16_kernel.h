@@ -54,6 +54,7 @@
 
 #include <utility>
 
+#include "key_splits.h"
 #include "kernel_params.h"
 #include "launch.h"
 #include "row_vis.h"
@@ -1311,23 +1312,23 @@ __global__ __launch_bounds__(NT, T::WGS) void attn_fwd_bf16_kernel(AttnParams p)
         jbeg = 0;
         jend = gp.hi - gp.lo;
     }
-    // This split's share of the visited tiles. An item with no more tiles than
-    // one split takes is written by its first split as if it were not split.
+    // This split's share of the visited tiles.
     [[maybe_unused]] auto lse_row = [&]() __attribute__((always_inline)) -> int64_t {
         return p.cu_q ? (int64_t)hq * p.total_q + qrow0 + qi : ((int64_t)it.b * p.hq + hq) * lq + qi;
     };
     [[maybe_unused]] bool partial = false;
     if constexpr (T::SPLIT) {
         const int sp = blockIdx.y;
-        partial = jend - jbeg > p.split_tiles;
-        jbeg += sp * p.split_tiles;
-        if (sp < p.splits - 1) jend = min(jend, jbeg + p.split_tiles);
+        const int tiles = jend - jbeg;
+        partial = split_share(p, sp, splittable(p, lq, krow0, lk), jbeg, jend);
         if (sp > 0 && jbeg >= jend) {  // no tiles: an empty partial
-            if (row_ok && lh == 0)
-                *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.ws_rows + lse_row()) * 4) =
+            if (partial && !p.cu_q && row_ok && lh == 0)
+                *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.part_stride + lse_row()) * 4) =
                     f32x4{-__builtin_inff(), 0.0f, 0.0f, 0.0f};
             return;
         }
+        if (sp == 0 && row_ok && lh == 0)
+            mark_row(p, lse_row(), partial, part_index(p, lse_row(), krow0, hq, qi), tiles);
     }
     // Relative-position reference: the row's first visible key for softmax
     // (largest bias; the shift is added back to the LSE), i' otherwise.
@@ -1536,7 +1537,7 @@ __global__ __launch_bounds__(NT, T::WGS) void attn_fwd_bf16_kernel(AttnParams p)
         if (partial) {
             // unnormalised O (ReLU, Sigmoid: the share of O) and the row's scalars
             if (row_ok) {
-                const int64_t prt = blockIdx.y * p.ws_rows + lse_row();
+                const int64_t prt = part_index(p, lse_row(), krow0, hq, qi) + blockIdx.y * p.part_stride;
                 float* prow = p.ws_o + prt * D;
                 const float scale = T::SOFTMAX ? 1.0f : inv;
 #pragma unroll
@@ -1556,8 +1557,6 @@ __global__ __launch_bounds__(NT, T::WGS) void attn_fwd_bf16_kernel(AttnParams p)
             }
             return;
         }
-        if (row_ok && lh == 0)  // written here: nothing to combine
-            *reinterpret_cast<f32x4*>(p.ws_ml + lse_row() * 4) = f32x4{0.0f, 0.0f, -1.0f, 0.0f};
     }
     if (row_ok) {
         __bf16* orow = ob + ooff + (int64_t)qi * p.so_s;

@@ -96,13 +96,26 @@ struct AttnParams {
     float cap_zmax;
     // Key splits: `splits` workgroups share the key tiles of one row tile,
     // split_tiles consecutive ones each, and leave partial results in the
-    // caller's workspace for attn_combine: ws_o [splits][ws_rows][D] and ws_ml
-    // [splits][ws_rows][4] (running max, fp32 row sum, the sum that normalises
-    // O, LSE shift), rows indexed as the LSE. splits = 1: no workspace.
+    // caller's workspace for attn_combine: ws_o [parts][D] and ws_ml [parts][4]
+    // (running max, fp32 row sum, the sum that normalises O, LSE shift).
+    // ws_rows counts the LSE's rows; splits = 1: no workspace.
+    // Fixed length: the partial of split s of row r is s * ws_rows + r, and a
+    // row that is not split has lo = -1 in its first one. Packed: only rows of
+    // sequences with more keys than a split takes (P = split_tiles tiles) have
+    // partials. Sequence b owns the slots of part_stride = hq * max_q rows from
+    // cu_k[b] / (P / 2) on: floor(2 L / P) of them at least for its L keys, no
+    // fewer than its ceil(L / P) splits when L > P. ws_mark holds (first
+    // partial, splits) of each row of the LSE, (-, 0) where it is not split.
     int32_t wide;            // bf16, D = 64: three workgroups per CU where compiled
     int32_t decode;          // bf16 decode kernel (num_q_tiles: its row tiles)
     int32_t splits, split_tiles;
-    int64_t ws_rows;
+    int64_t part_stride;     // fixed length: ws_rows
     float* ws_o;
     float* ws_ml;
+    int64_t ws_rows;
+    int32_t max_q;           // packed: longest query length
+    FastDiv div_part;        // packed: P / 2 keys
+    int64_t total_k;         // packed: key tokens
+    int64_t parts;
+    int32_t* ws_mark;
 };

@@ -39,6 +39,11 @@ CASES = [
                                                    softcap=50.0)),
     (128, 4, 2, [(1, 1), (4, 3000), (0, 50), (2, 0), (3, 700), (1, 512), (0, 0)], MASK_CAUSAL, {}),
     (64, 2, 4, [(1, 600), (1, 5), (1, 2500), (1, 64)], MASK_NONE, dict(alibi=True)),
+    # one long sequence first, amid and last among many short ones
+    (128, 4, 2, [(1, 9000)] + [(1, 7 + 5 * i) for i in range(40)], MASK_CAUSAL, {}),
+    (128, 4, 2, [(2, 9 + i) for i in range(25)] + [(4, 8100)] + [(1, 400 + i) for i in range(9)],
+     MASK_CAUSAL, dict(softcap=30.0)),
+    (64, 3, 2, [(1, 20 + i) for i in range(30)] + [(3, 7003)], MASK_NONE, {}),
 ]
 
 
@@ -127,6 +132,33 @@ def test_poisoned_lds_and_workspace_change_nothing(i):
 
 @pytest.mark.gpu
 @pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
+@pytest.mark.parametrize("lq,told", [(3, 2), (40, 32)])
+def test_sequence_with_more_rows_than_told_stays_in_the_workspace(lq, told):
+    """max_seqlen_q below a sequence's length: the rows that the grid covers are
+    right, and no partial result lands past the workspace (a guard behind it)."""
+    g = torch.Generator().manual_seed(lq)
+    q = torch.randn(1 + lq, 8, 128, generator=g).to(torch.bfloat16).cuda()
+    k, v = (torch.randn(12000, 2, 128, generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    cu = [torch.tensor(x, dtype=torch.int32, device="cuda") for x in ([0, 1, 1 + lq], [0, 6000, 12000])]
+    kw = dict(mask="none", cu_seqlens_q=cu[0], cu_seqlens_k=cu[1], max_seqlen_q=told, max_seqlen_k=6000)
+    out = torch.zeros_like(q)
+    d = attn.make_desc(q, k, v, out, **kw)
+    n = attn.load().attn_workspace_bytes(ctypes.byref(d))
+    assert n > 0
+    ws = torch.full((n + (1 << 22),), 255, dtype=torch.uint8, device="cuda")
+    assert attn.load().attn_fwd_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), None,
+                                   ctypes.byref(d), ws.data_ptr(), n) == 0
+    kw["max_seqlen_q"] = lq
+    want, _ = attn.fwd(q, k, v, **kw)
+    torch.cuda.synchronize()
+    assert (ws[n:] == 255).all()
+    rows = 1 + told
+    # another split of the keys, two bf16 roundings of |O| < 0.25
+    assert float((out[:rows].float() - want[:rows].float()).abs().max()) <= 2.0 ** -9
+
+
+@pytest.mark.gpu
+@pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
 def test_nan_query_row_stays_nan():
     """A NaN query gives NaN outputs for its row alone, split or not."""
     g = torch.Generator().manual_seed(1)
@@ -183,6 +215,34 @@ def test_workspace_bytes():
         _abi.STATUS_CODE["ATTN_ERR_BAD_SHAPE"]
     assert lib.attn_workspace_bytes(ctypes.byref(_desc(sched_order=3))) == \
         _abi.STATUS_CODE["ATTN_ERR_BAD_VARIANT"]
+
+
+def _packed_desc(hq, hkv, lens, **kw):
+    """A packed descriptor (dummy device arrays: only sizes are looked at)."""
+    return _desc(num_q_heads=hq, num_kv_heads=hkv, seqlen_q=0, seqlen_k=0, cu_seqlens_q=16,
+                 cu_seqlens_k=16, batch=len(lens), total_q=sum(a for a, _ in lens),
+                 total_k=sum(b for _, b in lens), max_seqlen_q=max(a for a, _ in lens),
+                 max_seqlen_k=max(b for _, b in lens), **kw)
+
+
+@pytest.mark.parametrize("hq,hkv,lens,kw", [
+    (128, 8, [(1, 384)] * 511 + [(1, 131072)], {}),
+    (32, 8, [(1, 384)] * 511 + [(1, 131072)], {}),
+    (128, 8, [(1, 750)] * 255 + [(1, 65536)], {}),
+    (32, 8, [(1, 84)] * 2047 + [(1, 32768)], {}),
+    (8, 8, [(100, 100)] * 299 + [(100, 60000)], {}),
+    (8, 1, [(150, 150)] * 499 + [(4000, 30000)], {}),
+    (8, 8, [(64, 64)] * 299 + [(64, 20000)], dict(dtype=_abi.ATTN_FP32)),
+    (8, 2, [(64, 64)] * 199 + [(8192, 8192)], dict(dtype=_abi.ATTN_FP32)),
+])
+def test_workspace_of_an_uneven_batch_is_bounded(hq, hkv, lens, kw):
+    """One long sequence among many short ones: the workspace follows the rows
+    that can be split, not every row times the longest one's splits (the first
+    case asked for 2.2 GB). A quarter of the inputs and outputs, or 64 MiB."""
+    need = attn.load().attn_workspace_bytes(ctypes.byref(_packed_desc(hq, hkv, lens, **kw)))
+    elt = 4 if kw else 2
+    io = 2 * 128 * elt * (hq * sum(a for a, _ in lens) + hkv * sum(b for _, b in lens))
+    assert 0 <= need <= max(64 << 20, io // 4)
 
 
 def test_misaligned_workspace_is_refused():

@@ -43,6 +43,9 @@ CASES = [
     ("fp32", 128, 2, 1, [(600, 600)], MASK_CAUSAL, dict(norm="sigmoid")),
     ("fp32", 64, 2, 2, [(33, 1600), (64, 64), (5, 900), (3, 0)], MASK_SHARE_QUESTION,
      dict(seg=[500, 1000])),
+    # one long sequence among short ones: only its rows have room in the workspace
+    ("bf16", 128, 2, 2, [(20, 90)] * 12 + [(130, 6000)] + [(40, 41)] * 3, MASK_CAUSAL, {}),
+    ("fp32", 64, 2, 2, [(65, 2500)] + [(9, 30)] * 10, MASK_CAUSAL, dict(norm="relu")),
 ]
 NORMS = {"softmax": 0, "relu": 1, "sigmoid": 2}
 
