@@ -15,6 +15,11 @@ from paper_2605_05023_amd.workloads import Inputs
 # Tolerances on the output O (max abs error) by dtype, and on LSE.
 O_TOL = {"bf16": 2e-2, "fp32": 1e-4}
 LSE_TOL = 1e-3
+# Bars on row_error. bf16: P and O are rounded with a relative 2^-9 at most each,
+# uniformly distributed, which adds up to sqrt(2/3) 2^-9 = 1.6e-3 of a row's norm
+# and to sqrt(2) as much where one value dominates. fp32: the score's D products
+# and the sums of P and P V, 2^-24 each, stay near 1e-6.
+ROW_TOL = {"bf16": 1e-2, "fp32": 1e-5}
 # ReLU / Sigmoid outputs are sums scaled by 1/L, of order 1/sqrt(L), so an
 # absolute bar would not test them: their error must stay within the same
 # fraction of the output's own scale, max|dO| <= O_TOL * max|O_ref|. The
@@ -82,6 +87,21 @@ def compare(inp: Inputs, o_gpu, lse_gpu, rows=None, *, o_tol=None, lse_tol=LSE_T
     fin = ~inf_ref
     lse_err = float(np.max(np.abs(lg[fin] - lrf[fin]))) if fin.any() else 0.0
     return o_err, lse_err, o_tol, lse_tol
+
+
+def row_error(got, ref):
+    """Largest relative error of an output row in the 2-norm, max |dO_i| / |O_i|
+    over the rows of the last axis. A row far below the others (under a tenth of
+    their median norm: O near zero by cancellation) is taken against that tenth.
+    Long rows average many values, so their own norm is the scale that a wrong
+    tile shows against."""
+    got = np.asarray(got, dtype=np.float64).reshape(-1, got.shape[-1])
+    ref = np.asarray(ref, dtype=np.float64).reshape(-1, ref.shape[-1])
+    norm = np.linalg.norm(ref, axis=-1)
+    if not (norm > 0).any():
+        return 0.0 if not got.any() else math.inf
+    least = 0.1 * float(np.median(norm[norm > 0]))
+    return float((np.linalg.norm(got - ref, axis=-1) / np.maximum(norm, least)).max())
 
 
 def assert_parity(inp, o_gpu, lse_gpu, rows=None, label="", **kw):

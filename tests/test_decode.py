@@ -5,8 +5,10 @@ waves take every fourth 32-key tile, and longer key ranges are split over
 workgroups when a workspace is given, so the cases sit around 32 flat rows,
 32 and 128 keys, and one and several splits with a ragged last one. Each runs
 with the workspace that `fwd` allocates and without one (attn_fwd); both are
-compared with the fp64 oracle element by element at the bars of the other
-parity tests, and with each other at twice the rounding of bf16 outputs.
+compared with the fp64 oracle, element by element at the bars of the other
+parity tests and row by row against the row's own norm, and with each other at
+twice the rounding of bf16 outputs. The launch plan of every case must name the
+decode kernel, and those with keys for more than one split must have a workspace.
 """
 import ctypes
 
@@ -16,7 +18,7 @@ import torch
 
 import oracle
 import paper_2605_05023_amd as attn
-from gpu_util import LSE_TOL, O_TOL, gpu_available, log
+from gpu_util import LSE_TOL, O_TOL, ROW_TOL, gpu_available, log, row_error
 from paper_2605_05023_amd import _abi
 from paper_2605_05023_amd.build import LIB_POISON
 from paper_2605_05023_amd.workloads import (MASK_CAUSAL, MASK_NAMES, MASK_NONE, MASK_PREFIX_LM,
@@ -44,6 +46,9 @@ CASES = [
     (128, 4, 2, [(2, 9 + i) for i in range(25)] + [(4, 8100)] + [(1, 400 + i) for i in range(9)],
      MASK_CAUSAL, dict(softcap=30.0)),
     (64, 3, 2, [(1, 20 + i) for i in range(30)] + [(3, 7003)], MASK_NONE, {}),
+    # a key cache stored token-major: the head stride is smaller than the row stride
+    (128, 4, 2, [(3, 1300)] * 2, MASK_CAUSAL, dict(token_major=True)),
+    (64, 8, 3, [(1, 47)] * 3, MASK_CAUSAL, dict(token_major=True)),
 ]
 
 
@@ -56,6 +61,8 @@ def _inputs(c):
     qs = (sum(lq), hq, D) if packed else (len(lens), hq, lq[0], D)
     ks = (sum(lk), hkv, D) if packed else (len(lens), hkv, lk[0], D)
     q, k, v = (torch.randn(s, generator=g).to(torch.bfloat16) for s in (qs, ks, ks))
+    if opt.get("token_major"):
+        k, v = (t.transpose(1, 2).contiguous().transpose(1, 2) for t in (k, v))
     kw = dict(mask=MASK_NAMES[mask], softcap=opt.get("softcap", 0.0),
               relative_position=opt.get("relpos", False), prefix_len=opt.get("prefix_len", 0))
     okw = dict(mask=mask, softcap=opt.get("softcap", 0.0), relpos=opt.get("relpos", False),
@@ -94,18 +101,25 @@ def _check(o, lse, o_ref, lse_ref, what):
     fin = np.isfinite(lse_ref)
     o_err = float(np.abs(og - o_ref).max()) if og.size else 0.0
     l_err = float(np.abs(lg[fin] - lse_ref[fin]).max()) if fin.any() else 0.0
-    log(f"  {what}: max|dO| = {o_err:.3e}, max|dLSE| = {l_err:.3e}")
-    assert o_err <= O_TOL["bf16"] and l_err <= LSE_TOL, what
+    r_err = row_error(og, o_ref)
+    log(f"  {what}: max|dO| = {o_err:.3e}, rows {r_err:.3e}, max|dLSE| = {l_err:.3e}")
+    assert o_err <= O_TOL["bf16"] and r_err <= ROW_TOL["bf16"] and l_err <= LSE_TOL, what
 
 
 @pytest.mark.parametrize("i", range(len(CASES)))
 @pytest.mark.gpu
 @pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
-def test_decode_parity(i):
+def test_decode_parity(i, capfd):
     c = CASES[i]
     log(f"[decode] {c}")
     q, k, v, packed, kw, okw = _inputs(c)
     qg, kg, vg = q.cuda(), k.cuda(), v.cuda()
+    attn.fwd(qg, kg, vg, log=True, **kw)
+    assert "| decode kernel" in capfd.readouterr().err
+    seen = max(min(b, sum(c[5].get("window", (b, 0))) + a) for a, b in c[3])  # keys of a row tile
+    need = attn.load().attn_workspace_bytes(
+        ctypes.byref(attn.make_desc(qg, kg, vg, torch.empty_like(qg), **kw)))
+    assert (need > 0) == (seen > 512), "split or whole"
     o, lse = attn.fwd(qg, kg, vg, **kw)
     o1, lse1 = _call(attn.load(), qg, kg, vg, packed, kw, False)
     torch.cuda.synchronize()
@@ -113,8 +127,8 @@ def test_decode_parity(i):
     _check(o, lse, o_ref, lse_ref, "with workspace")
     _check(o1, lse1, o_ref, lse_ref, "without")
     # P is rounded against another running max: two roundings of 2^-8 each
-    scale = max(1.0, float(np.abs(o_ref).max())) if o_ref.size else 1.0
-    assert float((o.float() - o1.float()).abs().max()) <= 2 * 2 ** -8 * scale
+    assert float((o.float() - o1.float()).abs().max()) <= 2 * 2 ** -8 * float(np.abs(o_ref).max())
+    assert row_error(o.float().cpu().numpy(), o1.float().cpu().numpy()) <= ROW_TOL["bf16"]
 
 
 @pytest.mark.parametrize("i", [0, 5, 9, 12, 13])

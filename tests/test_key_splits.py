@@ -6,7 +6,8 @@ with few keys, a packed sequence with a short cache), splits that hold no tile
 of a row, ragged last splits, every normalisation, the general mask path, the
 relative position's LSE shift and fp32. Each must really be split
 (attn_workspace_bytes > 0), is run on a workspace full of NaN, and is compared
-with the fp64 oracle element by element at the bars of the other parity tests.
+with the fp64 oracle, element by element at the bars of the other parity tests
+and row by row against the row's own norm.
 """
 import ctypes
 
@@ -16,11 +17,12 @@ import torch
 
 import oracle
 import paper_2605_05023_amd as attn
-from gpu_util import LSE_TOL, O_TOL, gpu_available, log
+from gpu_util import LSE_TOL, O_TOL, ROW_TOL, gpu_available, log, row_error
 from paper_2605_05023_amd import _abi
 from paper_2605_05023_amd.build import LIB_POISON
-from paper_2605_05023_amd.workloads import (MASK_CAUSAL, MASK_CAUSAL_BLOCKWISE, MASK_NAMES, MASK_NONE,
-                                            MASK_SHARE_QUESTION, MASK_SLIDING_WINDOW, alibi_slopes)
+from paper_2605_05023_amd.workloads import (MASK_CAUSAL, MASK_CAUSAL_BLOCKWISE, MASK_GLOBAL_WINDOW,
+                                            MASK_NAMES, MASK_NONE, MASK_PREFIX_LM, MASK_SHARE_QUESTION,
+                                            MASK_SLIDING_WINDOW, alibi_slopes)
 
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
@@ -46,6 +48,17 @@ CASES = [
     # one long sequence among short ones: only its rows have room in the workspace
     ("bf16", 128, 2, 2, [(20, 90)] * 12 + [(130, 6000)] + [(40, 41)] * 3, MASK_CAUSAL, {}),
     ("fp32", 64, 2, 2, [(65, 2500)] + [(9, 30)] * 10, MASK_CAUSAL, dict(norm="relu")),
+    # ALiBi without a soft-cap (its descending run of keys) across split boundaries
+    ("bf16", 128, 2, 2, [(150, 4000)], MASK_CAUSAL, dict(alibi=True)),
+    ("bf16", 64, 2, 2, [(2500, 2500)], MASK_CAUSAL, dict(alibi=True)),
+    # a prefix that ends inside a split, and leading global rows, which see every
+    # key where the other rows see their window
+    ("bf16", 128, 2, 2, [(300, 4000)], MASK_PREFIX_LM, dict(prefix_len=1500)),
+    ("fp32", 64, 2, 2, [(100, 1500)], MASK_PREFIX_LM, dict(prefix_len=1450)),
+    ("bf16", 128, 1, 1, [(2000, 2000)], MASK_GLOBAL_WINDOW, dict(window=(1500, 0), num_global=40)),
+    ("bf16", 64, 1, 1, [(2600, 2600)], MASK_GLOBAL_WINDOW, dict(window=(1900, 90), num_global=3,
+                                                               norm="sigmoid")),
+    ("fp32", 128, 1, 1, [(900, 900)], MASK_GLOBAL_WINDOW, dict(window=(600, 0), num_global=33)),
 ]
 NORMS = {"softmax": 0, "relu": 1, "sigmoid": 2}
 
@@ -81,9 +94,13 @@ def test_split_parity(i):
     q, k, v = (torch.randn(s, generator=g).to(tdt) for s in (qs, ks, ks))
     norm = opt.get("norm", "softmax")
     kw = dict(mask=MASK_NAMES[mask], softcap=opt.get("softcap", 0.0), norm=norm,
-              relative_position=opt.get("relpos", False), query_start=opt.get("query_start", 0))
+              relative_position=opt.get("relpos", False), query_start=opt.get("query_start", 0),
+              prefix_len=opt.get("prefix_len", 0), num_global=opt.get("num_global", 0))
     okw = dict(mask=mask, softcap=opt.get("softcap", 0.0), norm=NORMS[norm],
-               relpos=opt.get("relpos", False), query_start=opt.get("query_start", 0))
+               relpos=opt.get("relpos", False), query_start=opt.get("query_start", 0),
+               prefix_len=opt.get("prefix_len", 0))
+    if "num_global" in opt:
+        okw["global_tokens"] = list(range(opt["num_global"]))
     if "window" in opt:
         kw["window"] = opt["window"]
         okw.update(window_left=opt["window"][0], window_right=opt["window"][1])
@@ -109,8 +126,9 @@ def test_split_parity(i):
     o_err, tol = float(np.abs(og - o_ref).max()), O_TOL[dtype]
     if norm != "softmax":
         tol *= float(np.abs(o_ref).max())
-    log(f"  max|dO| = {o_err:.3e} (tol {tol:.1e})")
-    assert o_err <= tol
+    r_err = row_error(og, o_ref)
+    log(f"  max|dO| = {o_err:.3e} (tol {tol:.1e}), rows {r_err:.3e} (tol {ROW_TOL[dtype]:.1e})")
+    assert o_err <= tol and r_err <= ROW_TOL[dtype]
     if norm == "softmax":
         lg = lse.cpu().numpy().astype(np.float64)
         assert np.array_equal(np.isinf(lg), np.isinf(lse_ref))

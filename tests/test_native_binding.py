@@ -22,6 +22,20 @@ def _x(*shape, dtype=torch.bfloat16, seed=0):
     return torch.randn(*shape, generator=g).to(dtype).cuda()
 
 
+_ARGS = dict(causal=False, window=None, alibi_slopes=None, softcap=0.0, scale=None, cu_seqlens_q=None,
+             cu_seqlens_k=None, max_seqlen_q=None, max_seqlen_k=None, out=None, lse=None, return_lse=True,
+             mask=None, prefix_len=0, num_global=0, global_tokens=None, segment_starts=None, query_start=0,
+             relative_position=False, norm="softmax")
+
+
+def _native(*x, **kw):
+    """The call as the native path makes it; it must not be left to the Python path."""
+    assert not set(kw) - set(_ARGS)
+    res = attn._load_native().fwd(*x, *{**_ARGS, **kw}.values())
+    assert res is not NotImplemented
+    return res
+
+
 def _i32(v):
     return torch.tensor(v, dtype=torch.int32, device="cuda")
 
@@ -58,8 +72,7 @@ def _cases():
 def test_same_outputs_as_the_python_path():
     for i, (x, kw) in enumerate(_cases()):
         log(f"[native binding] case {i} {sorted(kw)}")
-        assert attn._load_native() is not None
-        got = attn.fwd(*x, **kw)
+        got = _native(*x, **kw)
         got = [t.clone() for t in (got if isinstance(got, tuple) else (got,))]
         want = attn.fwd(*x, **kw, validate=True)  # taken by the Python path
         want = want if isinstance(want, tuple) else (want,)
@@ -113,7 +126,7 @@ def test_no_memory_for_a_workspace(path):
     torch.cuda.synchronize()
     torch.cuda.empty_cache()  # segments of their own, with no room left in them
     q, k, v = _x(1, 32, 512, 128), _x(1, 32, 8192, 128), _x(1, 32, 8192, 128, seed=1)
-    kw = dict(validate=True) if path == "python" else {}
+    call = _native if path == "native" else lambda *x, **kw: attn.fwd(*x, validate=True, **kw)
     want, lse_want = attn.fwd(q, k, v)
     out, lse = torch.empty_like(q), torch.empty(1, 32, 512, device="cuda")
     torch.cuda.synchronize()
@@ -124,7 +137,7 @@ def test_no_memory_for_a_workspace(path):
             torch.empty(17 << 20, dtype=torch.uint8, device="cuda")
         torch.cuda.reset_peak_memory_stats()
         held = torch.cuda.memory_allocated()
-        attn.fwd(q, k, v, out=out, lse=lse, **kw)
+        call(q, k, v, out=out, lse=lse)
         assert torch.cuda.max_memory_allocated() == held  # no workspace
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
