@@ -40,7 +40,7 @@ constexpr int kBn = 32;    // keys per tile
 constexpr int kWaves = 4;
 
 template <int D, int CAP, int BIAS>
-__global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
+__global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void attn_decode_bf16_kernel(AttnParams p)
 {
     using T = Traits<D, kBn, CAP, BIAS, kNormSoftmax, false, true>;
     constexpr int ROWS_PER_KB = 1024 / T::ROWB;  // tile rows of one wave's direct load
@@ -97,8 +97,9 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
     const int f = min(f0 + li, nflat - 1);
     const bool row_ok = f0 + li < nflat;
     const int qi = (int)fast_div((uint32_t)f, p.div_group), hq = hkv * p.group + (f - qi * p.group);
-    const int64_t row = p.cu_q ? (int64_t)hq * p.total_q + qrow0 + qi
-                               : ((int64_t)b * p.hq + hq) * lq + qi;  // index of its LSE
+    auto lse_row = [&](int head, int query) __attribute__((always_inline)) -> int64_t {
+        return p.cu_q ? (int64_t)head * p.total_q + qrow0 + query : ((int64_t)b * p.hq + head) * lq + query;
+    };
 
     // Key tiles of the row tile, and this split's share of them.
     const int q0 = (int)fast_div((uint32_t)f0, p.div_group);
@@ -121,11 +122,11 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
         if (p.slopes) ws.bias_abs = -p.slopes[hq] * p.unit;
         if (p.relpos) ws.bias_lin = p.unit;
     }
-    const float lse_shift = ws.bias_lin != 0.0f ? (float)(ws.ip - ws.jref) : 0.0f;
+    auto lse_shift = [&]() { return ws.bias_lin != 0.0f ? (float)(ws.ip - ws.jref) : 0.0f; };
     if (sp > 0 && t_beg >= t_end) {  // no tiles: an empty partial
         if (partial && !p.cu_q && wave == 0 && lh == 0 && row_ok)
-            *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.part_stride + row) * 4) =
-                f32x4{-__builtin_inff(), 0.0f, 0.0f, lse_shift};
+            *reinterpret_cast<f32x4*>(p.ws_ml + (sp * p.part_stride + lse_row(hq, qi)) * 4) =
+                f32x4{-__builtin_inff(), 0.0f, 0.0f, lse_shift()};
         return;
     }
 
@@ -174,6 +175,11 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
     issue(kbuf, krs, krow, kt < t_end ? kt * kBn : lk);
     issue(vbuf, vrs, vrow, kt < t_end ? kt * kBn : lk);
     while (kt < t_end) {
+        // (not loop-invariant: the compiler would hold the distances of all of a
+        // tile's keys from them in registers through the loop, 154 of them at D =
+        // 64, which leaves room for three workgroups per CU: 942 groups of 2 heads
+        // with ALiBi and one key 8.7 us, 6.9 with four)
+        if constexpr (BIAS != kBiasNone) asm volatile("" : "+v"(ws.ip), "+v"(ws.jref));
         const int j0 = kt * kBn, nt = kt + kWaves;
         const int jn = nt < t_end ? nt * kBn : lk;  // past the last tile: rows of zeros
         __builtin_amdgcn_s_waitcnt(vmcnt_only(LW));  // K of this tile has landed (V may not)
@@ -260,6 +266,7 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
     const float inv = l_tot > 0.0f && lo_tot > 0.0f ? 1.0f / lo_tot : 0.0f;
     __bf16* orow = static_cast<__bf16*>(p.o) + (int64_t)hq * p.so_h +
                    (p.cu_q ? qrow0 + qi : qi) * p.so_s + (p.cu_q ? 0 : b * p.so_b);
+    const int64_t row = lse_row(hq, qi);
     const int64_t part = part_index(p, row, krow0, hq, qi), prt = part + sp * p.part_stride;
     float* prow = p.ws_o + prt * D;
 #pragma unroll
@@ -282,10 +289,10 @@ __global__ __launch_bounds__(NT, 2) void attn_decode_bf16_kernel(AttnParams p)
         }
     }
     if (wave == 0 && lh == 0) {
-        if (partial) *reinterpret_cast<f32x4*>(p.ws_ml + prt * 4) = f32x4{m_tot, l_tot, lo_tot, lse_shift};
+        if (partial) *reinterpret_cast<f32x4*>(p.ws_ml + prt * 4) = f32x4{m_tot, l_tot, lo_tot, lse_shift()};
         if (p.splits > 1 && sp == 0) mark_row(p, row, partial, part, gp.hi - gp.lo);
         if (!partial && p.lse)
-            p.lse[row] = l_tot > 0.0f ? (m_tot + __builtin_log2f(l_tot)) * kLn2 + lse_shift
+            p.lse[row] = l_tot > 0.0f ? (m_tot + __builtin_log2f(l_tot)) * kLn2 + lse_shift()
                                       : -__builtin_inff();
     }
 }
