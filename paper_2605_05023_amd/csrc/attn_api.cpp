@@ -22,12 +22,7 @@ namespace {
 // The most key splits of a row tile (attn_combine takes one per lane).
 constexpr int64_t kMaxSplits = 64;
 // Flat query rows (query heads of a kv group x queries) that the decode kernel
-// serves: always up to 64, and up to 128 while there are at most 256 kv groups.
-// Four row tiles beside one workgroup of the prefill kernel: 128 groups of 4
-// heads x 32 queries and 4000 keys 85 against 102 us, 64 groups of 128 queries
-// and 6000 keys 68 against 110, but 512 groups of 100 queries and 300 keys 21
-// against 14. At two row tiles (32 x 8 groups of 8 heads x 8 queries, 1000
-// keys) 28 against 100, at one head of 64 queries 57 against 57.
+// may take: up to 64, and up to 128 while there are at most 256 kv groups.
 constexpr int64_t kDecodeFlatRows = 64, kDecodeFlatRowsFew = 128, kDecodeFewGroups = 256;
 
 bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15u) == 0; }
@@ -416,16 +411,54 @@ int check_pointers(const attn_variant_desc& d, const AttnParams& p, const CallSh
     return ATTN_OK;
 }
 
-// Key tiles of `bn` keys that a row tile spanning `span` query positions can
-// touch, at most.
-int64_t max_key_tiles(const AttnParams& p, int64_t max_k, int64_t span, int64_t bn)
+// Keys that a row tile spanning `span` of max_q query positions can see, at
+// most (rows of leading global positions, which see all of them, apart). With a
+// left bound wl query i sees lq - i + wl keys at most, whatever the right one is.
+int64_t max_keys(const AttnParams& p, int64_t max_q, int64_t max_k, int64_t span)
 {
-    int64_t keys = max_k;
-    if (p.band.wl >= 0 && p.band.wr >= 0) {
-        const int64_t seen = (int64_t)p.band.wl + p.band.wr + span;
-        if (seen < keys) return seen / bn + 2;  // a run of keys that starts anywhere in a tile
-    }
-    return (keys + bn - 1) / bn;
+    if (p.band.wl < 0) return max_k;
+    int64_t seen = (int64_t)p.band.wl + max_q;
+    if (p.band.wr >= 0 && p.band.wr + span < max_q) seen = (int64_t)p.band.wl + p.band.wr + span;
+    return seen < max_k ? seen : max_k;
+}
+
+// Key tiles of `bn` keys that `keys` consecutive keys can touch, at most: those
+// of a window start anywhere in a tile.
+int64_t key_tiles(int64_t keys, int64_t max_k, int64_t bn)
+{
+    return keys < max_k ? keys / bn + 2 : (keys + bn - 1) / bn;
+}
+
+// Does the decode kernel take the call rather than the prefill kernel, which
+// would launch `blocks` workgroups? `units` row tiles of 32 flat rows against
+// `keys` keys. Graph-timed on both over 1..128 queries, groups of 1..8 heads,
+// 4..8192 kv groups and 16..3000 keys:
+//  * One 64-key tile of the prefill kernel (up to 64 keys): the decode kernel's
+//    merge of four waves costs 0.5-0.9 us (one head of 16..64 rows and keys 4.8
+//    against 5.6 us) and with more row tiles than prefill workgroups up to twice
+//    the time (1517 heads of 48 rows 18.5 against 37). It wins where the prefill
+//    kernel launches twice the workgroups, most of them empty (172 groups of 8
+//    heads x 1 query 12.1 against 4.6), and at D = 64 on large grids (6096
+//    heads x 16 queries 44 against 28).
+//  * Beyond, it wins where its row tiles leave no CU without one (16 groups of
+//    100 rows and 200 keys 8.4 against 7.3, 64 groups of 128 rows and 6000 keys
+//    110 against 68) or are no more than the prefill workgroups (128 groups of
+//    4 x 32 rows and 4000 keys 102 against 85; 256 groups of 8 heads x 8 rows
+//    and 1000 keys 100 against 28). With more row tiles it reads K and V more
+//    often (227 heads of 128 rows and keys 8.1 against 17); at D = 64, up to
+//    two a CU, 384 keys and more still pay (256 heads of 48 rows
+//    and 3000 keys 40 against 32, where the groups of an XCD share its L2).
+//  * D = 128 and up to 192 keys on a full chip: one wave's tile each is too
+//    little work for the merge (2048 heads of 32 rows and 128 keys 31 against
+//    35) unless prefill workgroups stay empty.
+bool decode_pays(int64_t D, int64_t keys, int64_t blocks, int64_t units, int64_t groups, int hp)
+{
+    if (keys <= 64) return (blocks > 256 && blocks >= 2 * units) ||
+                           (D == 64 && blocks > 512 && blocks >= units);
+    if (units <= 256) return true;
+    if (units > blocks)
+        return D == 64 && keys >= 384 && groups % 8 == 0 && (units <= 512 || 2 * units <= 3 * blocks);
+    return D == 64 || keys > 192 || blocks >= 2 * units || hp == 4;
 }
 
 int64_t workspace_need(const AttnParams& p, int64_t D)
@@ -462,19 +495,25 @@ void set_splits(AttnParams& p, int64_t D, int64_t bn, int64_t max_tiles, int64_t
     p.split_tiles = 1 << 30;
 }
 
-// Key splits of the decode kernel for `units` row tiles of max_tiles key tiles
-// at most and avg_tiles on average. A split and its combining launch cost about
-// 2.5 us, so up to 512 keys stay whole (300 keys: 6.7 us whole, 9.0 split).
-// Beyond, a split takes at least an eighth of the tiles, up to 512 keys (1000
-// keys, one sequence: 9.4 us in eight splits, 11.6 in two; 8192 keys: 13.7 us
-// in splits of 512, 14.4 of 256, 16.1 of 1024). Sequences of one length share
-// the chip evenly when there is one workgroup per CU (32 sequences of 1024
-// keys, 8 kv heads: 24.8 us whole, 29.5 in two splits); packed ones of uneven
-// length are cut into eight times as many pieces, so that the longest do not
-// outlast the rest (32 of 256..8192 keys: 138 us with 256 pieces aimed at, 119
-// with 1024, 116 with 2048).
-void split_decode(AttnParams& p, int64_t D, bool packed, int64_t units, int64_t max_tiles,
-                  int64_t avg_tiles, int64_t limit)
+// Key splits of the decode kernel for `units` row tiles (of `groups` kv groups)
+// of max_tiles key tiles at most and avg_tiles on average. Up to 512 keys stay
+// whole (300 keys: 6.7 us whole, 9.0 split). Beyond, a split takes at least an
+// eighth of the tiles, up to 512 keys (1000 keys, one sequence: 9.4 us in eight
+// splits, 11.6 in two; 8192 keys: 13.7 us in splits of 512, 14.4 of 256, 16.1 of
+// 1024). Sequences of one length share the chip evenly when there is one
+// workgroup per CU; packed ones of uneven length are cut into eight times as
+// many pieces, so that the longest do not outlast the rest (32 of 256..8192
+// keys: 138 us with 256 pieces aimed at, 119 with 1024, 116 with 2048).
+// The split is made when it saves more than it costs. Four tiles (a round of the
+// waves) take a workgroup 0.78 us (D = 64: 0.6), all K and V together at least
+// their bytes at 7 TB/s (half the CUs alone draw a tenth less), and the longest
+// row tile of an uneven batch half its time beyond that; a split adds 2.5 us for its second launch and the partial
+// rows at 2.5 TB/s. Over 444 split calls this chose the faster side but for 8 %
+// at most; without it 143 of them were slower split (192 groups of 4 x 16 rows
+// and 101..576 keys 23.1 us against 8.8 whole, 128 groups of 1000 keys 26.9
+// against 22.9).
+void split_decode(AttnParams& p, int64_t D, bool packed, int64_t groups, int64_t units,
+                  int64_t max_tiles, int64_t avg_tiles, int64_t limit)
 {
     if (max_tiles <= 16) return;
     const int64_t pieces = packed ? 2048 : 256;
@@ -485,6 +524,17 @@ void split_decode(AttnParams& p, int64_t D, bool packed, int64_t units, int64_t 
     if (least < floor_splits) least = floor_splits;
     if (per < least) per = least;
     per = (per + 3) / 4 * 4;  // whole rounds of the four waves
+    const int64_t splits = (max_tiles + per - 1) / per;
+    if (splits <= 1) return;
+    const double stream = (double)(groups * avg_tiles * attn::decode_keys()) * (double)D * 4.0 / 7e6;
+    auto run = [&](int64_t tiles) {
+        const double own = (double)((tiles + 3) / 4) * (D == 128 ? 0.78 : 0.6);
+        const double all = tiles == max_tiles && units <= 128 ? 1.1 * stream : stream;
+        return (own > all ? own : all) + (packed ? 0.5 * own : 0.0);
+    };
+    const int64_t usual = avg_tiles / per + 1 < splits ? avg_tiles / per + 1 : splits;
+    const double cost = 2.5 + (double)(p.ws_rows * usual) * (double)(D + 4) * 8.0 / 2.5e6;
+    if (run(max_tiles) - run(per) < cost) return;
     set_splits(p, D, attn::decode_keys(), max_tiles, per, limit);
 }
 
@@ -705,15 +755,17 @@ int plan_launch(const attn_variant_desc& d, AttnParams& p, const CallShape& c)
     const int64_t groups = (int64_t)d.batch * d.num_kv_heads;
     const int64_t flat = max_q * group, rt = (flat + attn::decode_rows() - 1) / attn::decode_rows();
     const bool scheduled = d.sched_heads_per_wg || d.sched_order || d.sched_chunk;
+    const int64_t tile_keys = max_keys(p, max_q, c.max_k, max_q);
     if (d.dtype == ATTN_BF16 && d.norm_kind == ATTN_NORM_SOFTMAX && closed_form_mask(d.mask_kind) &&
         !scheduled && groups * rt <= (1 << 20) &&
-        flat <= (groups <= kDecodeFewGroups ? kDecodeFlatRowsFew : kDecodeFlatRows)) {
+        flat <= (groups <= kDecodeFewGroups ? kDecodeFlatRowsFew : kDecodeFlatRows) &&
+        decode_pays(D, tile_keys, blocks, groups * rt, groups, hp)) {
         p.decode = 1;
         p.num_q_tiles = (int32_t)rt;
         p.div_group = make_fastdiv((uint32_t)group);
         const int64_t bn = attn::decode_keys();
         const int64_t avg_k = varlen ? d.total_k / d.batch : d.seqlen_k;
-        split_decode(p, D, varlen, groups * rt, max_key_tiles(p, c.max_k, max_q, bn),
+        split_decode(p, D, varlen, groups, groups * rt, key_tiles(tile_keys, c.max_k, bn),
                      (avg_k + bn - 1) / bn, limit);
         p.grid = (int32_t)(groups * rt);
     } else if (!scheduled && !p.gtok) {
@@ -723,11 +775,11 @@ int plan_launch(const attn_variant_desc& d, AttnParams& p, const CallShape& c)
         const int64_t usual_k = varlen ? d.total_k / d.batch : d.seqlen_k;
         const int64_t items =
             groups * (group / hp) * ((usual_q + block_m - 1) / block_m);
+        const int64_t tiles = key_tiles(max_keys(p, max_q, c.max_k, block_m), c.max_k, bn);
         // causal-like masks: the average row sees usual_k - usual_q / 2 keys
         const int64_t seen = d.mask_kind == ATTN_MASK_NONE ? usual_k : usual_k - usual_q / 2;
         const double tile_us = (D == 128 ? 0.85 : 0.5) * (bf16 ? 1.0 : 1.2);
-        split_underfilled(p, D, bn, items, max_key_tiles(p, c.max_k, block_m, bn), (seen + bn - 1) / bn,
-                          bf16 ? 8 : 4, tile_us, limit);
+        split_underfilled(p, D, bn, items, tiles, (seen + bn - 1) / bn, bf16 ? 8 : 4, tile_us, limit);
     }
     return ATTN_OK;
 }

@@ -7,8 +7,10 @@ workgroups when a workspace is given, so the cases sit around 32 flat rows,
 with the workspace that `fwd` allocates and without one (attn_fwd); both are
 compared with the fp64 oracle, element by element at the bars of the other
 parity tests and row by row against the row's own norm, and with each other at
-twice the rounding of bf16 outputs. The launch plan of every case must name the
-decode kernel, and those with keys for more than one split must have a workspace.
+twice the rounding of bf16 outputs. The launch plan must name the decode kernel
+for the cases of more than 64 keys, and for the last ones, whose few keys stand
+against many row tiles; those with keys for more than one split must have a
+workspace.
 """
 import ctypes
 
@@ -48,7 +50,11 @@ CASES = [
     (64, 3, 2, [(1, 20 + i) for i in range(30)] + [(3, 7003)], MASK_NONE, {}),
     # a key cache stored token-major: the head stride is smaller than the row stride
     (128, 4, 2, [(3, 1300)] * 2, MASK_CAUSAL, dict(token_major=True)),
-    (64, 8, 3, [(1, 47)] * 3, MASK_CAUSAL, dict(token_major=True)),
+    (64, 8, 3, [(1, 77)] * 3, MASK_CAUSAL, dict(token_major=True)),
+    # one 64-key tile of the prefill kernel: the decode kernel takes large grids
+    (64, 8, 16, [(1, 31)] * 12, MASK_CAUSAL, dict(many=True)),
+    (128, 4, 32, [(5, 3)] * 8, MASK_CAUSAL, dict(many=True)),  # rows that see no key
+    (64, 1, 64, [(33, 64)] * 20, MASK_CAUSAL, {}),  # more row tiles than prefill workgroups
 ]
 
 
@@ -115,11 +121,11 @@ def test_decode_parity(i, capfd):
     q, k, v, packed, kw, okw = _inputs(c)
     qg, kg, vg = q.cuda(), k.cuda(), v.cuda()
     attn.fwd(qg, kg, vg, log=True, **kw)
-    assert "| decode kernel" in capfd.readouterr().err
     seen = max(min(b, sum(c[5].get("window", (b, 0))) + a) for a, b in c[3])  # keys of a row tile
+    assert ("| decode kernel" in capfd.readouterr().err) == (seen > 64 or c[5].get("many", False))
     need = attn.load().attn_workspace_bytes(
         ctypes.byref(attn.make_desc(qg, kg, vg, torch.empty_like(qg), **kw)))
-    assert (need > 0) == (seen > 512), "split or whole"
+    assert (need > 0) == (seen > 513), "split or whole"
     o, lse = attn.fwd(qg, kg, vg, **kw)
     o1, lse1 = _call(attn.load(), qg, kg, vg, packed, kw, False)
     torch.cuda.synchronize()
@@ -257,6 +263,26 @@ def test_workspace_of_an_uneven_batch_is_bounded(hq, hkv, lens, kw):
     elt = 4 if kw else 2
     io = 2 * 128 * elt * (hq * sum(a for a, _ in lens) + hkv * sum(b for _, b in lens))
     assert 0 <= need <= max(64 << 20, io // 4)
+
+
+@pytest.mark.parametrize("kw,split", [
+    (dict(batch=1), True),
+    (dict(batch=64, seqlen_k=1000), False),  # 512 groups: the chip is full
+    (dict(batch=16, num_q_heads=8, seqlen_k=1000), False),
+    (dict(batch=1, num_q_heads=8, seqlen_q=128, seqlen_k=3000), True),
+    # a left bound alone leaves few keys to a decode step
+    (dict(mask_kind=_abi.ATTN_MASK_SLIDING_WINDOW, window_left=30, window_right=-1), False),
+    (dict(mask_kind=_abi.ATTN_MASK_SLIDING_WINDOW, window_left=3000, window_right=-1), True),
+])
+def test_a_split_is_made_where_it_saves_more_than_it_costs(kw, split):
+    assert (attn.load().attn_workspace_bytes(ctypes.byref(_desc(**kw))) > 0) == split
+
+
+@pytest.mark.parametrize("hq,hkv,lens", [(64, 16, [(16, 101)] * 11 + [(16, 576)]),
+                                         (8, 8, [(37, 144)] * 8 + [(37, 1166)] * 8)])
+def test_rows_too_many_to_split(hq, hkv, lens):
+    """Uneven packed chunks whose partial rows would take longer than the rest."""
+    assert attn.load().attn_workspace_bytes(ctypes.byref(_packed_desc(hq, hkv, lens, head_dim=64))) == 0
 
 
 def test_misaligned_workspace_is_refused():
