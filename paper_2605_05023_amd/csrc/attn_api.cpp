@@ -6,6 +6,7 @@
 // position arrays, copied to the host) before the launch.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -506,8 +507,9 @@ void set_splits(AttnParams& p, int64_t D, int64_t bn, int64_t max_tiles, int64_t
 // keys: 138 us with 256 pieces aimed at, 119 with 1024, 116 with 2048).
 // The split is made when it saves more than it costs. Four tiles (a round of the
 // waves) take a workgroup 0.78 us (D = 64: 0.6), all K and V together at least
-// their bytes at 7 TB/s (half the CUs alone draw a tenth less), and the longest
-// row tile of an uneven batch half its time beyond that; a split adds 2.5 us for its second launch and the partial
+// their bytes at 7 TB/s (half the CUs alone draw a tenth less), a workgroup's
+// dispatch 4.5 ns (those of short rows' empty splits too), and the longest row
+// tile of an uneven batch half its time beyond that; a split adds 2.5 us for its second launch and the partial
 // rows at 2.5 TB/s. Over 444 split calls this chose the faster side but for 8 %
 // at most; without it 143 of them were slower split (192 groups of 4 x 16 rows
 // and 101..576 keys 23.1 us against 8.8 whole, 128 groups of 1000 keys 26.9
@@ -527,14 +529,15 @@ void split_decode(AttnParams& p, int64_t D, bool packed, int64_t groups, int64_t
     const int64_t splits = (max_tiles + per - 1) / per;
     if (splits <= 1) return;
     const double stream = (double)(groups * avg_tiles * attn::decode_keys()) * (double)D * 4.0 / 7e6;
-    auto run = [&](int64_t tiles) {
+    auto run = [&](int64_t tiles, int64_t cuts) {
         const double own = (double)((tiles + 3) / 4) * (D == 128 ? 0.78 : 0.6);
-        const double all = tiles == max_tiles && units <= 128 ? 1.1 * stream : stream;
-        return (own > all ? own : all) + (packed ? 0.5 * own : 0.0);
+        const double all = cuts == 1 && units <= 128 ? 1.1 * stream : stream;
+        const double dispatch = (double)(units * cuts) * 0.0045;
+        return std::max({own, all, dispatch}) + (packed ? 0.5 * own : 0.0);
     };
-    const int64_t usual = avg_tiles / per + 1 < splits ? avg_tiles / per + 1 : splits;
+    const int64_t usual = std::min(avg_tiles / per + 1, splits);
     const double cost = 2.5 + (double)(p.ws_rows * usual) * (double)(D + 4) * 8.0 / 2.5e6;
-    if (run(max_tiles) - run(per) < cost) return;
+    if (run(max_tiles, 1) - run(per, splits) < cost) return;
     set_splits(p, D, attn::decode_keys(), max_tiles, per, limit);
 }
 
