@@ -6,7 +6,7 @@
 // makes the same checks on the tensors themselves, fills the descriptor,
 // allocates out, lse and the workspace, and calls the C ABI. Host time a call
 // 19.4 -> 6.1 us with one launch (the launch itself takes 4), 23.4 -> 9.9 with
-// a key split; 1 x 32/8 heads x 333 tokens 18.5 -> 9.9 us a call (now the
+// a key split; 1 x 32/8 heads x 333 tokens 18.3 -> 9.7 us a call (now the
 // kernel's time).
 //
 // It only takes calls that need nothing else: plain device tensors, checked
@@ -277,7 +277,9 @@ bool call(PyObject* const* a, at::Tensor* out, at::Tensor* lse, bool* with_lse, 
         try {
             ws = at::empty({bytes}, q.options().dtype(at::kByte));
         } catch (const c10::OutOfMemoryError&) {
-            // no room for a workspace: the call is computed without the split
+            // No room for a workspace: the call is computed without the split. The
+            // allocator frees its cached blocks before it gives up, which waits for
+            // the GPU: a process at its memory limit pays that on every such call.
         }
     }
     *status = g_fwd_ws(q.const_data_ptr(), k.const_data_ptr(), v.const_data_ptr(),

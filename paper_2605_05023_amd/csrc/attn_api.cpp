@@ -548,10 +548,13 @@ void split_decode(AttnParams& p, int64_t D, bool packed, int64_t groups, int64_t
 // split shortens the longest by saved us; against that stand the second launch
 // and the writing and reading of the partial rows (about 2.5 TB/s), and it is
 // made when it saves a third more than it costs. 32 heads of 256 queries and
-// 8192 keys (64 workgroups): 114 us whole, 49 in 4 splits; 8 heads of 512
-// queries, 4096 keys, D = 64: 45 and 20; 16 heads of 2048 causal rows (256
+// 8192 keys (64 workgroups): 115 us whole, 51 in 4 splits; 8 heads of 512
+// queries, 4096 keys, D = 64: 44 and 19; 16 heads of 2048 causal rows (256
 // workgroups): 37 whole, 50 in splits of 16 tiles. fp32, 8 heads, one query,
-// 4000 keys: 133 and 17.
+// 4000 keys: 142 and 26. The segments of an index mask are not known here: 17 of
+// 106 share-question calls, whose rows see few of the keys, lost up to 20 % to
+// their second launch, the others won up to 85 %; taking two or three even shares
+// of the keys as what a row sees lost as many of either.
 void split_underfilled(AttnParams& p, int64_t D, int64_t bn, int64_t items, int64_t max_tiles,
                        int64_t avg_tiles, int64_t least, double tile_us, int64_t limit)
 {
@@ -739,8 +742,8 @@ int plan_launch(const attn_variant_desc& d, AttnParams& p, const CallShape& c)
     }
     // Third workgroup per CU for D = 64 (where compiled: no score mods, no left
     // bound) on long sequences and grids of about three rounds and more: 4 x 16
-    // heads of 3000 causal rows 95 -> 90 us, 4096 164 -> 157, 2 x 16 x 8000
-    // without a mask 554 -> 545; below, its spills at start-up and the uneven
+    // heads of 3000 causal rows 99 -> 90 us, 4096 165 -> 153, 2 x 16 x 8000
+    // without a mask 555 -> 528 (36 shapes: 10 % faster to 1 % slower); below, its spills at start-up and the uneven
     // last round cost more (4 x 16 x 1000 18.6 against 20.2, 32 x 16 x 500 41.7
     // against 43.6, packed lengths of 100..3000 182 against 183).
     p.wide = D == 64 && p.grid >= 1500 && (varlen ? d.total_k / d.batch : d.seqlen_k) >= 2560;
@@ -828,7 +831,11 @@ extern "C" int attn_fwd_ws(const void* q, const void* k, const void* v, void* ou
     p.o = out;
     p.lse = lse;
     const int64_t need = workspace_need(p, d.head_dim);
-    if (need > 0 && (!workspace || workspace_bytes < need)) {  // one workgroup per row tile
+    // One workgroup per row tile without a workspace. The decode kernel still
+    // gains on the prefill kernel then: 8 groups of 4 heads, one query and 8192
+    // keys 111 -> 52 us, 8 heads of 600 keys 12.3 -> 8.5 (251 shapes: 0.10-0.77 of
+    // its time).
+    if (need > 0 && (!workspace || workspace_bytes < need)) {
         p.splits = 1;
         p.split_tiles = 1 << 30;
     } else if (need > 0) {

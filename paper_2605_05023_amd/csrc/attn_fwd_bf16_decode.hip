@@ -21,9 +21,9 @@
 //    one, V during the next K Q^T: no workgroup barrier in the loop, 8 to 16
 //    KiB in flight per wave and eight waves per CU.
 // Bound by memory: one step of 32 sequences of 256..8192 cached tokens (8 kv
-// heads, D = 128, 540 MB of K and V) takes 114 us (4.7 TB/s; a large copy moves
+// heads, D = 128, 540 MB of K and V) takes 115 us (4.7 TB/s; a large copy moves
 // 4.9) where the prefill kernel took 169; one sequence of 8192 tokens with 128
-// query heads 14 us against 109 (it ran 32 workgroups).
+// query heads 14 us against 111 (it ran 32 workgroups).
 // The products, their layouts and the LDS swizzle are those of the prefill
 // kernel (bf16_kernel.h) with 32-key tiles; the running max is exact on every
 // tile, and O is normalised by the sum of P as rounded to bf16. Closed-form

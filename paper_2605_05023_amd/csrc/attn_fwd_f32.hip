@@ -30,9 +30,9 @@
 // the chip, so the work items are kept small: 128-row workgroups (one 32-row
 // block and all keys per wave) measured 4 % faster only for 2 x 16 heads of
 // 4096 rows without a mask (2090 against 2184 us) and slower elsewhere (2 x 16
-// causal heads of 1000 rows at D = 128: 139 against 100 us), and sum longer
+// causal heads of 1000 rows at D = 128: 1.4 times the time), and sum longer
 // chains (relative error 1.3e-6 against 7.1e-7). The vector-FMA kernel before
-// took 411 us (20 TFLOP/s) there. The score modifications, the masks with tile skipping, the base-2 online softmax
+// took 410 us (20 TFLOP/s) there, this one 91. The score modifications, the masks with tile skipping, the base-2 online softmax
 // and the ReLU / Sigmoid normalisations are the same as in the bf16 kernel (Eq.
 // 1 and 2 of Section 2.2, Appendix A). On the general mask path each lane
 // derives its row's visible keys (row_vis.h) and the wave visits the tiles
