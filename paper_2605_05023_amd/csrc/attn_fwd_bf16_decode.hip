@@ -106,7 +106,8 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void attn_decode_bf16_kernel(A
     const int q1 = (int)fast_div((uint32_t)min(f0 + kRows, nflat) - 1u, p.div_group);
     const TilePlan gp = plan_tiles(p.band, q0, q1 - q0 + 1, lq, lk, kBn);
     int t_beg = gp.lo, t_end = gp.hi;
-    const bool partial = split_share(p, (int)sp, splittable(p, lq, krow0, lk), t_beg, t_end);
+    bool partial = false;
+    if (p.splits > 1) partial = split_share(p, (int)sp, splittable(p, lq, krow0, lk), t_beg, t_end);
 
     WaveState<T> ws;
     ws.lh = lh;
@@ -267,7 +268,11 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void attn_decode_bf16_kernel(A
     __bf16* orow = static_cast<__bf16*>(p.o) + (int64_t)hq * p.so_h +
                    (p.cu_q ? qrow0 + qi : qi) * p.so_s + (p.cu_q ? 0 : b * p.so_b);
     const int64_t row = lse_row(hq, qi);
-    const int64_t part = part_index(p, row, krow0, hq, qi), prt = part + sp * p.part_stride;
+    int64_t part = 0, prt = 0;
+    if (p.splits > 1) {
+        part = part_index(p, row, krow0, hq, qi);
+        prt = part + sp * p.part_stride;
+    }
     float* prow = p.ws_o + prt * D;
 #pragma unroll
     for (int i0 = 0; i0 < T::DBLK; i0 += 2) {
