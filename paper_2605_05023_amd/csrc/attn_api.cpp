@@ -446,9 +446,12 @@ int64_t key_tiles(int64_t keys, int64_t max_k, int64_t bn)
 //    110 against 68) or are no more than the prefill workgroups (128 groups of
 //    4 x 32 rows and 4000 keys 102 against 85; 256 groups of 8 heads x 8 rows
 //    and 1000 keys 100 against 28). With more row tiles it reads K and V more
-//    often (227 heads of 128 rows and keys 8.1 against 17); at D = 64, up to
-//    two a CU, 384 keys and more still pay (256 heads of 48 rows
-//    and 3000 keys 40 against 32, where the groups of an XCD share its L2).
+//    often (227 heads of 128 rows and keys 8.1 against 17); where the groups of an XCD share
+//    its L2, long key ranges still pay: 384 keys and more at D = 64, up to two
+//    row tiles a CU (256 heads of 48 rows and 3000 keys 40 against 32), 2048 at
+//    D = 128 while the prefill kernel fills half the CUs at most (128 heads of
+//    128 rows and 3000 keys 48 against 44, 1024 keys 20 against 20; 256 heads
+//    of 64 rows and 8192 keys 183 against 203).
 //  * D = 128 and up to 192 keys on a full chip: one wave's tile each is too
 //    little work for the merge (2048 heads of 32 rows and 128 keys 31 against
 //    35) unless prefill workgroups stay empty.
@@ -458,7 +461,9 @@ bool decode_pays(int64_t D, int64_t keys, int64_t blocks, int64_t units, int64_t
                            (D == 64 && blocks > 512 && blocks >= units);
     if (units <= 256) return true;
     if (units > blocks)
-        return D == 64 && keys >= 384 && groups % 8 == 0 && (units <= 512 || 2 * units <= 3 * blocks);
+        return groups % 8 == 0 &&
+               (D == 64 ? keys >= 384 && (units <= 512 || 2 * units <= 3 * blocks)
+                        : keys >= 2048 && groups <= 128);
     return D == 64 || keys > 192 || blocks >= 2 * units || hp == 4;
 }
 

@@ -137,6 +137,31 @@ def test_decode_parity(i, capfd):
     assert row_error(o.float().cpu().numpy(), o1.float().cpu().numpy()) <= ROW_TOL["bf16"]
 
 
+@pytest.mark.parametrize("d,group,b,lq,lk,decode", [
+    (64, 1, 32, 48, 384, True), (64, 1, 32, 48, 383, False),    # two row tiles a CU
+    (128, 1, 16, 97, 2048, True), (128, 1, 16, 97, 2047, False),  # half the CUs
+    (128, 1, 8, 100, 200, True), (128, 1, 9, 128, 200, False),  # a row tile for every CU
+    (64, 2, 17, 1, 33, True), (64, 2, 16, 1, 33, False),        # one 64-key tile
+    (128, 1, 33, 32, 193, True), (128, 1, 33, 32, 192, False),  # a tile for every wave
+])
+@pytest.mark.gpu
+@pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
+def test_route(d, group, b, lq, lk, decode, capfd):
+    """Both sides of the rules that choose the kernel, against the prefill kernel
+    (a schedule override keeps it), with a window that starts inside a tile."""
+    g = torch.Generator(device="cuda").manual_seed(lk)
+    q, k, v = (torch.randn(b, h, n, d, generator=g, device="cuda").to(torch.bfloat16)
+               for h, n in ((8 * group, lq), (8, lk), (8, lk)))
+    attn.fwd(q, k, v, causal=True, log=True)
+    assert ("| decode kernel" in capfd.readouterr().err) == decode
+    for kw in (dict(causal=True), dict(window=(lk - 7, 3))):
+        o, lse = attn.fwd(q, k, v, **kw)
+        o1, lse1 = attn.fwd(q, k, v, order="natural", **kw)
+        torch.cuda.synchronize()
+        assert row_error(o.float().cpu().numpy(), o1.float().cpu().numpy()) <= ROW_TOL["bf16"]
+        assert float((lse - lse1).abs().max()) <= LSE_TOL
+
+
 @pytest.mark.parametrize("i", [0, 5, 9, 12, 13])
 @pytest.mark.gpu
 @pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
